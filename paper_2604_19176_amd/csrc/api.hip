@@ -16,8 +16,6 @@
 using namespace pat;
 
 
-static unsigned xcd_grid(int items) { return (unsigned)(((items + kXcds - 1) / kXcds) * kXcds); }
-
 // Dynamic LDS of the interpolation ([8][cb + 7] float2 window) and of the
 // spread (2 cb staged points x 19 words).
 static size_t spread_lds(int cb, int ib) { return sizeof(float) * spread_lds_words(2 * cb, ib); }
@@ -137,19 +135,7 @@ static int forward_run(const pat_plan* p, const float* f, float* g, int batch, v
     }
     if ((rc = check_launch())) return rc;
     prof_mark(p, 0, 3, st);
-    {
-        const int rt = d.ring_spec ? 1 : c.ring_rt;  // compile-time ring kernels: one ring per workgroup
-        const dim3 grid(xcd_grid((d.nlam + rt - 1) / rt * batch)), blk(p->thr_ring);
-        if (d.ring_spec && d.ring_spec_grp == 2)
-            hipLaunchKernelGGL((k_ring_fwd_spec<2, 1>), grid, blk, p->lds_ring, st, d, p->ws, wsp, batch);
-        else if (d.ring_spec && d.ring_spec_grp == 1)
-            hipLaunchKernelGGL((k_ring_fwd_spec<1, 1>), grid, blk, p->lds_ring, st, d, p->ws, wsp, batch);
-        else if (d.ring_spec && p->thr_ring == ring_spec_threads(0, 2))
-            hipLaunchKernelGGL((k_ring_fwd_spec<0, 2>), grid, blk, p->lds_ring, st, d, p->ws, wsp, batch);
-        else if (d.ring_spec)
-            hipLaunchKernelGGL((k_ring_fwd_spec<0, 1>), grid, blk, p->lds_ring, st, d, p->ws, wsp, batch);
-        else hipLaunchKernelGGL(k_ring_fwd, grid, blk, p->lds_ring, st, d, p->ws, wsp, c.ring_rt, batch);
-    }
+    ring_fwd_launch(p, wsp, batch, st);
     if ((rc = check_launch())) return rc;
     prof_mark(p, 0, 4, st);
     const int qd = d.syn_dense ? 5 : 4;  // event index after the synthesis
@@ -185,19 +171,7 @@ static int adjoint_run(const pat_plan* p, const float* g, float* f, int batch, v
         if ((rc = check_launch())) return rc;
         prof_mark(p, 1, 2, st);
     }
-    {
-        const int rt = d.ring_spec ? 1 : c.ring_rt;
-        const dim3 grid(xcd_grid((d.nlam + rt - 1) / rt * batch)), blk(p->thr_ring);
-        if (d.ring_spec && d.ring_spec_grp == 2)
-            hipLaunchKernelGGL((k_ring_adj_spec<2, 1>), grid, blk, p->lds_ring, st, d, p->ws, wsp, batch);
-        else if (d.ring_spec && d.ring_spec_grp == 1)
-            hipLaunchKernelGGL((k_ring_adj_spec<1, 1>), grid, blk, p->lds_ring, st, d, p->ws, wsp, batch);
-        else if (d.ring_spec && p->thr_ring == ring_spec_threads(0, 2))
-            hipLaunchKernelGGL((k_ring_adj_spec<0, 2>), grid, blk, p->lds_ring, st, d, p->ws, wsp, batch);
-        else if (d.ring_spec)
-            hipLaunchKernelGGL((k_ring_adj_spec<0, 1>), grid, blk, p->lds_ring, st, d, p->ws, wsp, batch);
-        else hipLaunchKernelGGL(k_ring_adj, grid, blk, p->lds_ring, st, d, p->ws, wsp, c.ring_rt, batch);
-    }
+    ring_adj_launch(p, wsp, batch, st);
     if ((rc = check_launch())) return rc;
     prof_mark(p, 1, 2 + qa, st);
     {
@@ -726,8 +700,7 @@ extern "C" int pat_batch_forward(const pat_batch* b, const float* const* f_ptrs,
         }
     }
     if ((rc = check_launch())) return rc;
-    hipLaunchKernelGGL(k_ring_fwd_b, dim3(xcd_grid(batch_items(b, kStRing))), dim3(b->thr_ring), b->lds_ring, st,
-                       bt, w);
+    ring_fwd_b_launch(bt, w, batch_items(b, kStRing), b->thr_ring, b->lds_ring, st);
     if ((rc = check_launch())) return rc;
     if (batch_items(b, kStSynFwd) > 0) {
         hipLaunchKernelGGL(k_syn_dense_fwd_b, dim3(xcd_grid(batch_items(b, kStSynFwd))), dim3(kSynThreads), 0, st,
@@ -755,8 +728,7 @@ extern "C" int pat_batch_adjoint(const pat_batch* b, const float* const* g_ptrs,
                            bt, w);
         if ((rc = check_launch())) return rc;
     }
-    hipLaunchKernelGGL(k_ring_adj_b, dim3(xcd_grid(batch_items(b, kStRing))), dim3(b->thr_ring), b->lds_ring, st,
-                       bt, w);
+    ring_adj_b_launch(bt, w, batch_items(b, kStRing), b->thr_ring, b->lds_ring, st);
     if ((rc = check_launch())) return rc;
     {
         const dim3 grid(xcd_grid(batch_items(b, kStSpread)));

@@ -21,45 +21,12 @@
 // floating-point atomics anywhere: every sum has a fixed order, so results are
 // bitwise repeatable.
 #include "cfft.hpp"
+#include "device_util.hpp"
 #include "fft.hpp"
 #include "pat_internal.hpp"
 
 namespace pat {
 
-
-// XCD-aware work mapping.  The hardware hands workgroup w to XCD (w mod 8);
-// remap so that XCD x owns the contiguous item range [start(x), start(x+1))
-// of the U work items (instance-major), keeping one instance's intermediates
-// in one XCD's L2.  Returns -1 for the padding workgroups of the last round.
-constexpr int kXcds = 8;
-__device__ __forceinline__ int xcd_item(int w, int U)
-{
-    const int x = w % kXcds, q = w / kXcds;
-    const int Q = U / kXcds, Rm = U - Q * kXcds;
-    const int cnt = Q + (x < Rm ? 1 : 0);
-    if (q >= cnt) return -1;
-    return x * Q + min(x, Rm) + q;
-}
-
-// The 8 taps of the ES kernel phi(t) = exp(beta (sqrt(1 - (2t/w)^2) - 1)) at
-// t = frac + 3 - d (d = 0..7, frac in [0, 1)): z = t / 4 lies in [-1, 1], so
-// 1 - z^2 only needs a clamp against rounding below 0; the hardware square
-// root and base-2 exponential (about 1 ulp each) are used directly, since the
-// argument of the exponential lies in [-beta log2(e), 0].  The same routine
-// serves the interpolation and the spread, which keeps them exact transposes.
-__device__ __forceinline__ void es_weights8(float frac, float (&w)[8])
-{
-    constexpr float kb = (float)(kEsBeta * 1.4426950408889634);  // beta log2(e)
-    const float z0 = frac * 0.25f;
-#pragma unroll
-    for (int d = 0; d < 8; ++d) {
-        const float z = z0 + 0.25f * (float)(3 - d);
-        const float q = fmaxf(fmaf(-z, z, 1.0f), 0.0f);
-        w[d] = __builtin_amdgcn_exp2f(fmaf(kb, __builtin_amdgcn_sqrtf(q), -kb));
-    }
-}
-
-__device__ __forceinline__ int fbits(float v) { return __float_as_int(v); }
 
 // Deterministic block sum (fixed tree); every thread gets the total.
 __device__ float block_sum(float v, float* scratch)
@@ -92,42 +59,6 @@ __device__ __forceinline__ float wave0_fixed_sum(const float* __restrict__ v, in
     for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
     return s;
 }
-
-struct InstPtrs {
-    char* ws;         // workspace base of instance 0
-    size_t stride;    // bytes per instance
-};
-
-// st(t, ld(t)) for t < count by the workgroup (t = t0 + threadIdx.x + j blockDim.x,
-// U values of t per thread and chunk).  A chunk issues all of a thread's loads
-// before its first store, and no load sits under a divergent branch (indices
-// past the end are clamped to count - 1 and their values dropped), so a chunk
-// waits for one memory latency instead of one per element.
-template <int U, class Ld, class St>
-__device__ __forceinline__ void fill_batched(int count, Ld ld, St st)
-{
-    const int tid = threadIdx.x, bd = blockDim.x;
-    for (int t0 = 0; t0 < count; t0 += U * bd) {
-        decltype(ld(0)) v[U];
-#pragma unroll
-        for (int j = 0; j < U; ++j) v[j] = ld(min(t0 + tid + j * bd, count - 1));
-#pragma unroll
-        for (int j = 0; j < U; ++j) {
-            const int t = t0 + tid + j * bd;
-            if (t < count) st(t, v[j]);
-        }
-    }
-}
-
-struct IdxVal {
-    int i;
-    float2 v;
-};
-
-struct IdxF {
-    int i;
-    float v;
-};
 
 // ---------------------------------------------------------------------------
 // The grid transforms (length Ng, `nseq` sequences at stride ld in LDS): with
@@ -288,24 +219,6 @@ __device__ __forceinline__ void rowpass_fwd_tile(const PlanDev& d, const WsLayou
 }
 
 // ---------------------------------------------------------------------------
-// Ring kernels.  One workgroup handles RT consecutive radial frequencies
-// (rings) of one instance, one ring after another:
-//   forward: the ring's interpolated half-plane values (k_gather), completion
-//            F(l + Npsi/2) = conj F(l), angular FFT,
-//            a_k = c_k e^{i k theta_0} i^k J_k(lam_n R) W_n F_k / Npsi (k <= K_n),
-//            synthesis over detectors h(d) = Re sum_k a_k e^{i k d dtheta}
-//            (one inverse FFT of length P after folding k mod P when
-//            dtheta = 2 pi / P, else Bluestein with two FFTs of length L),
-//            -> hT[n][d]  (real; the cosine transform over n follows)
-//   adjoint: the exact transpose, ending with the Hermitian fold -> H,
-//            stored in band order for the spread, which applies the conjugate
-//            half-pixel phase as it stages each point from a band-order table
-//            (scattered writes here, contiguous reads there: reading
-//            H through each band-order point's ring index instead makes every
-//            wave-load of the spread touch tens of cache lines per instance,
-//            which costs the spread more than the scatter costs here).
-// ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
 // forward: ES interpolation of the half spectrum at the half-plane polar
 // points.  Points are visited in band order (sorted by footprint base row r0,
 // then base column bx); a tile is TH bands x CB columns: the points with r0
@@ -398,661 +311,6 @@ __device__ __forceinline__ void gather_tile(const PlanDev& d, const WsLayout& L,
             }
             ((float2*)(wbs[b] + L.polar))[ri] = cmul(acc, ph);
         }
-    }
-}
-
-__device__ __forceinline__ float2 mul_ipow(float2 v, int k)  // v * i^k
-{
-    switch (k & 3) {
-        case 0: return v;
-        case 1: return make_float2(-v.y, v.x);
-        case 2: return make_float2(-v.x, -v.y);
-        default: return make_float2(v.y, -v.x);
-    }
-}
-
-// Unpack one bin of a real length-2H DFT from Z = FFT_H(z), z(t) = q(2t) + i q(2t+1):
-//   Q_k = (Z_k + conj Z_{H-k}) / 2 - (i/2) w_{2H}^k (Z_k - conj Z_{H-k}),  0 <= k < H.
-__device__ __forceinline__ float2 real_unpack(const float2* Z, int H, int k, float2 wk)
-{
-    const float2 zk = Z[k];
-    const float2 zc = cconj(Z[k == 0 ? 0 : H - k]);
-    const float2 sm = cadd(zk, zc), df = csub(zk, zc);
-    const float2 t = cmul(wk, df);
-    return make_float2(0.5f * (sm.x + t.y), 0.5f * (sm.y - t.x));
-}
-
-// Layout of the ring kernels' dynamic LDS (float2 slots, ring_lds_slots):
-// sa (ring FFT; the half-length synthesis buffer sc shares it), sy
-// (synthesis), and the two-level twiddles of lengths Npsi(n) (twN) and S
-// (twA) used outside the transforms.  The transforms read their per-pass
-// twiddles, and the mode loops the ring's coefficients, from global memory
-// (tables shared by all instances of a plan, cache resident): small LDS per
-// ring keeps many rings resident per CU, and nothing is held in registers
-// across a transform.
-struct RingLds {
-    float2 *sa, *sc, *sy, *twN, *twA;
-};
-
-__device__ __forceinline__ RingLds ring_lds(float2* sm, const PlanDev& d)
-{
-    RingLds r;
-    const int Pmax = d.npsi_max / 2;
-    const int S = d.syn_len;
-    const int B1 = max(Pmax, d.syn_half ? S / 2 : 0);
-    const int B2 = max(S, Pmax);
-    r.sa = sm;
-    r.sc = sm;
-    r.sy = sm + B1;
-    r.twN = r.sy + B2;
-    r.twA = r.twN + ring_tw_slots(d.npsi_max);
-    return r;
-}
-
-__device__ __forceinline__ void ring_fwd_tile(const PlanDev& d, const WsLayout& L, char* wb, int tile, int RT,
-                                              float2* sm)
-{
-    const float2* __restrict__ Fp = (const float2*)(wb + L.polar);
-    float* hT = (float*)(wb + L.hdet);  // [nlam][D]
-    const int D = d.D, S = d.syn_len;
-    const int tid = threadIdx.x, bd = blockDim.x;
-    const RingLds R = ring_lds(sm, d);
-    const int n0 = tile * RT;
-    const int nr = min(RT, d.nlam - n0);
-    // synthesis: fold with even P -> transform of P/2 + twiddles of P (twA); else transform of S
-    const TwLds twA = d.syn_dense ? TwLds{R.twA, R.twA, 0} : tw_lds_build(R.twA, d.ffts[d.fft_syn], d.tw);
-    const FftDev& fS = d.ffts[d.fft_synh];
-    const float2* __restrict__ tbS = d.tw + fS.tb;
-    for (int r = 0; r < nr; ++r) {
-        const int n = n0 + r;
-        const int off = d.ring_off[n], P = d.ring_off[n + 1] - off;
-        const int Kn = d.ring_K[n];
-        const float2* __restrict__ cf = d.coef + d.ring_joff[n];
-        float* hn = hT + (size_t)n * D;
-        const FftDev& fR = d.ffts[d.ring_fft[n]];
-        const float2* __restrict__ tbR = d.tw + fR.tb;
-        const FftDev& fN = d.ffts[d.ring_twn[n]];
-        // the ring's inputs, all loads in flight together: twiddles w_{2P}^k (twN)
-        // and the polar values, packed as follows:
-        // q(m) = Re F + Im F (m < P), Re F - Im F (m >= P) is real; z(t) = q(2t) + i q(2t+1)
-        const TwFetch twf = tw_lds_fetch(fN, d.tw);
-        fill_batched<kRingFillUnroll>(
-            P,
-            [&](int t) {
-                float qv[2];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int m = 2 * t + u;
-                    const bool lo = m < P;
-                    const float2 F = Fp[off + (lo ? m : m - P)];
-                    qv[u] = lo ? F.x + F.y : F.x - F.y;
-                }
-                return make_float2(qv[0], qv[1]);
-            },
-            [&](int t, float2 v) { R.sa[t] = v; });
-        const TwLds twN = tw_lds_store(R.twN, fN, d.tw, twf);
-        __syncthreads();
-        fft_lds<false, kRingFftMaxButterflies>(R.sa, P, 1, fR, tbR);
-        if (d.syn_dense) {
-            // explicit detector angles: the mode coefficients a_k go to the workspace;
-            // the dense product with the cos/sin table synthesises the detectors
-            float2* am = (float2*)(wb + L.modes) + (size_t)n * d.Kp;
-            fill_batched<kRingFillUnroll>(
-                Kn + 1, [&](int k) { return cmul(cf[k], real_unpack(R.sa, P, k, twN(k))); },
-                [&](int k, float2 v) { am[k] = v; });
-            __syncthreads();
-            continue;
-        }
-        // y = the a_k = coef_k Q_k (Q: the real length-2P transform of q) folded
-        // mod Pf (fold) or zero-padded to S (chirp-z), summed in order of k: pass
-        // 0 writes k < Pf, each further pass adds the next Pf modes
-        const int Pf = d.fold_P ? d.fold_P : S;
-        for (int q = tid; q < Pf; q += bd)
-            if (q > Kn) R.sy[q] = make_float2(0.f, 0.f);
-        for (int base = 0; base <= Kn; base += Pf) {
-            if (base) __syncthreads();
-            fill_batched<kRingFillUnroll>(
-                min(Kn + 1 - base, Pf),
-                [&](int t) {
-                    const int k = base + t;
-                    const float2 a = cmul(cf[k], real_unpack(R.sa, P, k, twN(k)));
-                    return base ? cadd(R.sy[t], a) : a;
-                },
-                [&](int t, float2 v) { R.sy[t] = v; });
-        }
-        __syncthreads();
-        if (d.fold_P) {
-            if (d.syn_half) {
-                // Re(IFFT_P(y)) as a half-length inverse FFT of the Hermitian part
-                const int H2 = Pf / 2;
-                fill_batched<kRingFillUnroll>(
-                    H2,
-                    [&](int sidx) {
-                        const int s1 = sidx, s2 = sidx + H2;
-                        const float2 y1 = R.sy[s1], y1c = cconj(R.sy[s1 == 0 ? 0 : Pf - s1]);
-                        const float2 y2 = R.sy[s2], y2c = cconj(R.sy[Pf - s2]);
-                        const float2 h1 = cscale(cadd(y1, y1c), 0.5f), h2 = cscale(cadd(y2, y2c), 0.5f);
-                        const float2 E = cadd(h1, h2);
-                        const float2 O = cmulc(csub(h1, h2), twA(sidx));  // times e^{+2 pi i s / P}
-                        return make_float2(E.x - O.y, E.y + O.x);         // E + i O
-                    },
-                    [&](int sidx, float2 v) { R.sc[sidx] = v; });
-                __syncthreads();
-                fft_lds<true, kRingFftMaxButterflies>(R.sc, H2, 1, fS, tbS);
-                // detector q is point s q of the P-point grid
-                fill_batched<kRingFillUnroll>(
-                    D,
-                    [&](int q) {
-                        const int j = q * d.fold_s;
-                        const float2 z = R.sc[j >> 1];
-                        return (j & 1) ? z.y : z.x;
-                    },
-                    [&](int q, float v) { hn[q] = v; });
-            } else {
-                fft_lds<true, kRingFftMaxButterflies>(R.sy, Pf, 1, fS, tbS);
-                fill_batched<kRingFillUnroll>(
-                    D, [&](int q) { return R.sy[q * d.fold_s].x; }, [&](int q, float v) { hn[q] = v; });
-            }
-        } else {
-            fft_lds<false, kRingFftMaxButterflies>(R.sy, S, 1, fS, tbS);
-            for (int q = tid; q < S; q += bd) R.sy[q] = cmul(R.sy[q], d.czt_vhat[q]);
-            __syncthreads();
-            fft_lds<true, kRingFftMaxButterflies>(R.sy, S, 1, fS, tbS);
-            for (int q = tid; q < D; q += bd) {
-                const float2 v = R.sy[q], w = d.czt_post[q];
-                hn[q] = w.x * v.x - w.y * v.y;
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// Value at point j of the P-point angular grid of the detector values placed
-// at points s q (q < D), zero elsewhere.
-__device__ __forceinline__ float grid_det(const float* hn, int j, int s, float rcp_s, int D)
-{
-    int q = j, rem = 0;
-    if (s != 1) fdivmod(j, s, rcp_s, q, rem);
-    const float v = hn[min(q, D - 1)];  // unconditional load (batched by the caller), value selected
-    return (rem == 0 && q < D) ? v : 0.f;
-}
-
-__device__ __forceinline__ void ring_adj_tile(const PlanDev& d, const WsLayout& L, char* wb, int tile, int RT,
-                                              float2* sm)
-{
-    const float* hT = (const float*)(wb + L.hdet);  // [nlam][D]
-    float2* Hb = (float2*)(wb + L.polar);
-    const int D = d.D, S = d.syn_len;
-    const int tid = threadIdx.x, bd = blockDim.x;
-    const RingLds R = ring_lds(sm, d);
-    const int n0 = tile * RT;
-    const int nr = min(RT, d.nlam - n0);
-    const bool half = d.fold_P && d.syn_half;
-    const float rcp_s = 1.0f / (float)max(d.fold_s, 1);
-    const float rcp_P = __builtin_amdgcn_rcpf((float)max(d.fold_P, 1));  // fdivmod makes k mod P exact
-    // the mode values Q~ go to qb, the Hermitian-part input of the ring's inverse FFT to eb
-    float2* const qb = half ? R.sy : R.sa;
-    float2* const eb = half ? R.sa : R.sy;
-    const TwLds twA = d.syn_dense ? TwLds{R.twA, R.twA, 0} : tw_lds_build(R.twA, d.ffts[d.fft_syn], d.tw);
-    const FftDev& fS = d.ffts[d.fft_synh];
-    const float2* __restrict__ tbS = d.tw + fS.tb;
-    for (int r = 0; r < nr; ++r) {
-        const int n = n0 + r;
-        const int off = d.ring_off[n], P = d.ring_off[n + 1] - off;
-        const int Kn = d.ring_K[n];
-        const float2* __restrict__ cf = d.coef + d.ring_joff[n];
-        const float* hn = hT + (size_t)n * D;
-        // explicit detector angles: y~_k from the dense product (workspace), no transform
-        const float2* __restrict__ am = (const float2*)(wb + L.modes) + (size_t)n * d.Kp;
-        const FftDev& fR = d.ffts[d.ring_fft[n]];
-        const float2* __restrict__ tbR = d.tw + fR.tb;
-        const FftDev& fN = d.ffts[d.ring_twn[n]];
-        const TwFetch twf = tw_lds_fetch(fN, d.tw);
-        // the ring's inputs, all loads in flight together: twiddles (twN) and the
-        // detector values zero-padded to the synthesis length; then y~ = their
-        // FFT.  Explicit angles: Q~ directly.
-        if (d.syn_dense) {
-            fill_batched<kRingFillUnroll>(
-                Kn + 1, [&](int k) { return cmulc(am[k], cf[k]); }, [&](int k, float2 v) { qb[k] = v; });
-            tw_lds_store(R.twN, fN, d.tw, twf);
-        } else if (half) {
-            const int H2 = d.fold_P / 2;
-            fill_batched<kRingFillUnroll>(
-                H2,
-                [&](int t) {
-                    return make_float2(grid_det(hn, 2 * t, d.fold_s, rcp_s, D), grid_det(hn, 2 * t + 1, d.fold_s, rcp_s, D));
-                },
-                [&](int t, float2 v) { R.sc[t] = v; });
-            tw_lds_store(R.twN, fN, d.tw, twf);
-            __syncthreads();
-            fft_lds<false, kRingFftMaxButterflies>(R.sc, H2, 1, fS, tbS);
-        } else if (d.fold_P) {
-            fill_batched<kRingFillUnroll>(
-                S, [&](int t) { return make_float2(grid_det(hn, t, d.fold_s, rcp_s, D), 0.f); },
-                [&](int t, float2 v) { R.sy[t] = v; });
-            tw_lds_store(R.twN, fN, d.tw, twf);
-            __syncthreads();
-            fft_lds<false, kRingFftMaxButterflies>(R.sy, S, 1, fS, tbS);
-        } else {
-            fill_batched<kRingFillUnroll>(
-                S,
-                [&](int q) {
-                    const int qc = min(q, D - 1);
-                    const float2 v = cmulc(make_float2(hn[qc], 0.f), d.czt_post[qc]);
-                    return q < D ? v : make_float2(0.f, 0.f);
-                },
-                [&](int q, float2 v) { R.sy[q] = v; });
-            tw_lds_store(R.twN, fN, d.tw, twf);
-            __syncthreads();
-            fft_lds<false, kRingFftMaxButterflies>(R.sy, S, 1, fS, tbS);
-            for (int q = tid; q < S; q += bd) R.sy[q] = cmulc(R.sy[q], d.czt_vhat[q]);
-            __syncthreads();
-            fft_lds<true, kRingFftMaxButterflies>(R.sy, S, 1, fS, tbS);
-        }
-        const TwLds twN{R.twN, R.twN + 64, 0};
-        // y~ at synthesis index sidx (0 <= sidx < S)
-        auto ytil = [&](int sidx) {
-            if (!half) return R.sy[sidx];
-            const int Pf = d.fold_P, H2 = Pf / 2;
-            if (sidx == H2) return make_float2(R.sc[0].x - R.sc[0].y, 0.f);
-            const bool hi = sidx > H2;
-            const int s0 = hi ? Pf - sidx : sidx;
-            const float2 v = real_unpack(R.sc, H2, s0, twA(s0));
-            return hi ? cconj(v) : v;
-        };
-        // Q~_k = conj(coef_k) y~_{k mod Pf}
-        if (!d.syn_dense) {
-            fill_batched<kRingFillUnroll>(
-                Kn + 1,
-                [&](int k) {
-                    int sidx = k, fq;
-                    if (d.fold_P) fdivmod(k, d.fold_P, rcp_P, fq, sidx);
-                    return cmulc(ytil(sidx), cf[k]);
-                },
-                [&](int k, float2 v) { qb[k] = v; });
-        }
-        __syncthreads();
-        // Re(IFFT_{2P}(Q~)) as a half-length inverse FFT: E + i O from the
-        // Hermitian part of Q~ (which vanishes above K_n < P).
-        // Q~_h[s] = Q~[s]/2 (0 < s <= K), Re Q~[0] (s = 0); Q~_h[s + P] = conj Q~[P - s]/2 (P - s <= K).
-        fill_batched<kRingFillUnroll>(
-            P,
-            [&](int sidx) {
-                // reads clamped into qb[0 .. Kn], values outside the mode range dropped
-                const float2 q1 = qb[min(sidx, Kn)], q2 = qb[min(P - sidx, Kn)];
-                const float2 zero = make_float2(0.f, 0.f);
-                const float2 a = sidx == 0 ? make_float2(q1.x, 0.f) : (sidx <= Kn ? cscale(q1, 0.5f) : zero);
-                const float2 c = (sidx != 0 && P - sidx <= Kn) ? cscale(cconj(q2), 0.5f) : zero;
-                const float2 E = cadd(a, c);
-                const float2 O = cmulc(csub(a, c), twN(sidx));
-                return make_float2(E.x - O.y, E.y + O.x);
-            },
-            [&](int sidx, float2 v) { eb[sidx] = v; });
-        __syncthreads();
-        fft_lds<true, kRingFftMaxButterflies>(eb, P, 1, fR, tbR);
-        // q~(m): m = 2t -> Re z_t, m = 2t + 1 -> Im z_t;  F~_h(l) = (q~(l) + q~(l+P)) + i (q~(l) - q~(l+P))
-        fill_batched<kRingFillUnroll>(
-            P,
-            [&](int l) {
-                const float2 z1 = eb[l >> 1];
-                const float a = (l & 1) ? z1.y : z1.x;
-                const int m = l + P;
-                const float2 z2 = eb[m >> 1];
-                const float c = (m & 1) ? z2.y : z2.x;
-                const float2 Fh = make_float2(a + c, a - c);
-                return IdxVal{d.band_of[off + l], Fh};
-            },
-            [&](int, IdxVal iv) { Hb[iv.i] = iv.v; });
-        __syncthreads();
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Ring kernels with compile-time transforms (plans with ring_spec: a uniform
-// arc whose pitch is 2 pi s / P with P even, modes folded mod P, every length
-// with a cfft.hpp plan).  The same operator as ring_fwd_tile /
-// ring_adj_tile; lanes 0..63 of wave 0 do all the work in one LDS buffer of
-// max(Npsi_max, P) / 2 complex values:
-//   forward: head<Pn> (packed ring -> ring transform -> modes times their
-//            coefficients, folded, straight into the half-length synthesis
-//            input), synthesis transform (length P/2), tail (detectors);
-//   adjoint: head (detectors -> synthesis transform), tail<Pn> (mode
-//            coefficients straight into the half-length input of the ring's
-//            inverse transform, transform, band-order stores).
-// Each mode is evaluated once: the synthesis input at s and P/2 - s (forward),
-// or the ring input at u and Pn - u (adjoint), need the same modes, so one
-// lane computes both.  Twiddles come from the plan's FP64-computed tables.
-// ---------------------------------------------------------------------------
-struct RingSpecArgs {
-    int off, Kn;
-    const float2* __restrict__ cf;   // ring coefficients coef_k, k <= K_n
-    const float2* __restrict__ ctwR; // ring transform table
-    const float2* __restrict__ uw;   // w_{2 Pn}^k, k = 0..Pn
-};
-
-__device__ __forceinline__ RingSpecArgs ring_spec_args(const PlanDev& d, int n)
-{
-    RingSpecArgs a;
-    a.off = d.ring_off[n];
-    a.Kn = d.ring_K[n];
-    a.cf = d.coef + d.ring_joff[n];
-    a.ctwR = d.ctw + d.ring_ctw[n];
-    a.uw = d.ctw + d.ring_uw[n];
-    return a;
-}
-
-// E + i O of the real-output half-length synthesis at index s (0 <= s <= P/2)
-// from y_s, y_{P-s}, y_{s+P/2}, y_{P/2-s} (y_q = a_q, q <= K_n; 0 above)
-__device__ __forceinline__ float2 syn_prologue(float2 y1, float2 y1m, float2 y2, float2 y2m, float2 w)
-{
-    const float2 h1 = cscale(cadd(y1, cconj(y1m)), 0.5f), h2 = cscale(cadd(y2, cconj(y2m)), 0.5f);
-    const float2 E = cadd(h1, h2);
-    const float2 O = cmulc(csub(h1, h2), w);  // times e^{+2 pi i s / P}
-    return make_float2(E.x - O.y, E.y + O.x);
-}
-
-template <int Pn, int T>
-__device__ __forceinline__ void ring_fwd_spec_head(const PlanDev& d, const float2* __restrict__ Fp,
-                                                   const RingSpecArgs& a, float2* buf, float2* syn)
-{
-    const int lane = threadIdx.x;
-    const bool act = lane < T;
-    // the ring's half-plane values packed as the real sequence q(m) = Re F + Im F
-    // (m < Pn), Re F - Im F (m >= Pn), z(t) = q(2t) + i q(2t + 1)
-    if (act) {
-        constexpr int RND = (Pn + T - 1) / T;
-        float2 v[RND];
-#pragma unroll
-        for (int i = 0; i < RND; ++i) {
-            const int t = min(lane + i * T, Pn - 1);
-            const int m0 = 2 * t, m1 = 2 * t + 1;
-            const float2 F0 = Fp[a.off + (m0 < Pn ? m0 : m0 - Pn)];
-            const float2 F1 = Fp[a.off + (m1 < Pn ? m1 : m1 - Pn)];
-            v[i] = make_float2(m0 < Pn ? F0.x + F0.y : F0.x - F0.y, m1 < Pn ? F1.x + F1.y : F1.x - F1.y);
-        }
-#pragma unroll
-        for (int i = 0; i < RND; ++i) {
-            const int t = lane + i * T;
-            if (Pn % T == 0 || t < Pn) buf[t] = v[i];
-        }
-    }
-    __syncthreads();
-    cfft<Pn, false, cfft_wg_lanes(Pn, T)>(buf, a.ctwR, lane, lane < cfft_wg_lanes(Pn, T));
-    // a_k = coef_k Q_k for k <= K_n (zero above), in place of Z: the pair (k, Pn - k)
-    // shares sm = Z_k + conj Z_{Pn-k}, df = Z_k - conj Z_{Pn-k} and t = w_{2Pn}^k df,
-    //   Q_k = sm/2 - (i/2) t,  Q_{Pn-k} = conj(sm)/2 - (i/2) conj(t)
-    // (w_{2Pn}^{Pn-k} = -conj w_{2Pn}^k)
-    // (each lane reads and writes only its own pair's two slots)
-    if (act) {
-        constexpr int PAIRS = Pn / 2 + 1;  // k = 0 .. Pn/2
-#pragma unroll
-        for (int i = 0; i < (PAIRS + T - 1) / T; ++i) {
-            const int k0 = lane + i * T;
-            const int k = min(k0, PAIRS - 1);
-            const int kc = k == 0 ? 0 : Pn - k;
-            const float2 zk = buf[k];
-            const float2 zc = cconj(buf[kc]);
-            const float2 sm = cadd(zk, zc), df = csub(zk, zc);
-            const float2 t = cmul(a.uw[k], df);
-            const float2 Q1 = make_float2(0.5f * (sm.x + t.y), 0.5f * (sm.y - t.x));
-            const float2 Q2 = make_float2(0.5f * (sm.x - t.y), 0.5f * (-sm.y - t.x));
-            const float2 c1 = a.cf[min(k, a.Kn)], c2 = a.cf[min(kc, a.Kn)];
-            const float2 v1 = k <= a.Kn ? cmul(c1, Q1) : make_float2(0.f, 0.f);
-            const float2 v2 = kc <= a.Kn ? cmul(c2, Q2) : make_float2(0.f, 0.f);
-            if (PAIRS % T == 0 || k0 < PAIRS) {
-                buf[k] = v1;
-                if (k != 0 && 2 * k != Pn) buf[kc] = v2;
-            }
-        }
-    }
-    __syncthreads();
-    const int Pf = d.fold_P, SH = Pf >> 1;
-    // y_q = sum of a_k over k = q mod Pf, k < Pn (a_k = 0 above K_n), in increasing k
-    auto mode = [&](int q) {
-        float2 y = q < Pn ? buf[q] : make_float2(0.f, 0.f);
-        for (int k = q + Pf; k < Pn; k += Pf) y = cadd(y, buf[k]);
-        return y;
-    };
-    const float2* __restrict__ sw = d.ctw + d.syn_sw;
-    const int items = (SH + 1) >> 1;
-    if (act) {
-        for (int s = lane; s < items; s += T) {
-            if (s == 0) {
-                const float2 y0 = mode(0), yh = mode(SH), yq = mode(SH >> 1), y3 = mode(SH + (SH >> 1));
-                syn[0] = syn_prologue(y0, y0, yh, yh, sw[0]);
-                if ((SH & 1) == 0) syn[SH >> 1] = syn_prologue(yq, y3, y3, yq, sw[SH >> 1]);
-            } else {
-                const float2 ya = mode(s), yb = mode(Pf - s), yc = mode(s + SH), yd = mode(SH - s);
-                syn[s] = syn_prologue(ya, yb, yc, yd, sw[s]);
-                syn[SH - s] = syn_prologue(yd, yc, yb, ya, sw[SH - s]);
-            }
-        }
-    }
-    __syncthreads();
-}
-
-template <int T>
-__device__ __forceinline__ void ring_fwd_spec_tail(const PlanDev& d, const float2* buf, float* hn)
-{
-    const int lane = threadIdx.x;
-    if (lane < T) {
-        // detector q is point s q of the P-point grid: Re part at even, Im at odd points
-        for (int q0 = 0; q0 < d.D; q0 += 4 * T) {
-            float v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int q = min(q0 + lane + u * T, d.D - 1);
-                const int j = q * d.fold_s;
-                const float2 z = buf[j >> 1];
-                v[u] = (j & 1) ? z.y : z.x;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int q = q0 + lane + u * T;
-                if (q < d.D) hn[q] = v[u];
-            }
-        }
-    }
-    __syncthreads();
-}
-
-template <int G, int W>
-__device__ __forceinline__ void ring_fwd_spec_tile(const PlanDev& d, const WsLayout& L, char* wb, int n, float2* buf)
-{
-    // one ring per workgroup: a loop over rings would keep every length's
-    // synthesis twiddles live across it
-    const float2* __restrict__ Fp = (const float2*)(wb + L.polar);
-    float* hT = (float*)(wb + L.hdet);  // [nlam][D]
-    float2* syn = buf + d.npsi_max / 2;  // the synthesis input after the ring buffer
-    const RingSpecArgs a = ring_spec_args(d, n);
-    const int Pn = d.ring_off[n + 1] - a.off;
-    constexpr int T = ring_spec_threads(G, W);
-    switch (Pn) {
-#define PAT_RING_FWD_HEAD(LEN) \
-    case LEN: ring_fwd_spec_head<LEN, T>(d, Fp, a, buf, syn); break;
-        PAT_CFFT_LENGTHS_LO(PAT_RING_FWD_HEAD)
-        default:
-            if constexpr (G >= 1) {
-                switch (Pn) {
-                    PAT_CFFT_LENGTHS_HI(PAT_RING_FWD_HEAD)
-                    default:
-                        if constexpr (G >= 2) {
-                            switch (Pn) {
-                                PAT_CFFT_LENGTHS_HI2(PAT_RING_FWD_HEAD)
-                                default: break;
-                            }
-                        }
-                        break;
-                }
-            }
-            break;
-#undef PAT_RING_FWD_HEAD
-    }
-    cfft_run_wg<true, G, T>(syn, d.fold_P >> 1, d.ctw + d.syn_ctw);
-    ring_fwd_spec_tail<T>(d, syn, hT + (size_t)n * d.D);
-}
-
-template <int T>
-__device__ __forceinline__ void ring_adj_spec_head(const PlanDev& d, const float* __restrict__ hn, float2* buf)
-{
-    const int lane = threadIdx.x;
-    const int SH = d.fold_P >> 1, fs = d.fold_s, D = d.D;
-    // the detector values at points s q of the P-point grid (zero between), packed
-    // as z(t) = h(2t) + i h(2t + 1)
-    if (lane < T) {
-        const float rcp_s = __builtin_amdgcn_rcpf((float)fs);
-        for (int t0 = 0; t0 < SH; t0 += 2 * T) {
-            float2 v[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int t = min(t0 + lane + u * T, SH - 1);
-                float h[2];
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int j = 2 * t + e;
-                    int q = j, rem = 0;
-                    if (fs != 1) fdivmod(j, fs, rcp_s, q, rem);
-                    const float x = hn[min(q, D - 1)];
-                    h[e] = (rem == 0 && q < D) ? x : 0.f;
-                }
-                v[u] = make_float2(h[0], h[1]);
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int t = t0 + lane + u * T;
-                if (t < SH) buf[t] = v[u];
-            }
-        }
-    }
-    __syncthreads();
-}
-
-template <int Pn, int T>
-__device__ __forceinline__ void ring_adj_spec_tail(const PlanDev& d, const RingSpecArgs& a, float2* syn,
-                                                   float2* buf, float2* Hb)
-{
-    const int lane = threadIdx.x;
-    const bool act = lane < T;
-    const int Pf = d.fold_P, SH = Pf >> 1;
-    const float2* __restrict__ sw = d.ctw + d.syn_sw;
-    // the ring points' band-order slots, for the stores at the end: loaded now,
-    // in flight during the transforms
-    constexpr int RO = (Pn + T - 1) / T;
-    int slot[RO];
-#pragma unroll
-    for (int i = 0; i < RO; ++i) slot[i] = d.band_of[a.off + min(lane + i * T, Pn - 1)];
-    // y~ at synthesis index q (0 <= q <= P/2) from the half-length transform Z,
-    // in place of Z (slot P/2 after it): the pair (s, SH - s) shares
-    // sm = Z_s + conj Z_{SH-s}, df = Z_s - conj Z_{SH-s}, t = w_P^s df,
-    //   y~_s = sm/2 - (i/2) t,  y~_{SH-s} = conj(sm)/2 - (i/2) conj(t),
-    // and y~_{SH} = Re Z_0 - Im Z_0; above P/2, y~_{P-q} = conj y~_q
-    // (each lane reads and writes only its own pair's slots)
-    float2* ys = syn;
-    if (act) {
-        const int PAIRS = SH / 2 + 1;  // s = 0 .. SH/2
-        for (int s = lane; s < PAIRS; s += T) {
-            const int sc = s == 0 ? 0 : SH - s;
-            const float2 zk = ys[s];
-            const float2 zc = cconj(ys[sc]);
-            const float2 sm = cadd(zk, zc), df = csub(zk, zc);
-            const float2 t = cmul(sw[s], df);
-            ys[s] = make_float2(0.5f * (sm.x + t.y), 0.5f * (sm.y - t.x));
-            if (s == 0) ys[SH] = make_float2(zc.x + zc.y, 0.f);
-            else if (2 * s != SH) ys[sc] = make_float2(0.5f * (sm.x - t.y), 0.5f * (-sm.y - t.x));
-        }
-    }
-    __syncthreads();
-    // Q~_k = conj(coef_k) y~_{k mod P} for k <= K_n (0 above)
-    auto qmode = [&](int k) {
-        const int kc = min(k, a.Kn);
-        int kf = kc;  // synthesis index k mod Pf
-        while (kf >= Pf) kf -= Pf;
-        const bool hi = kf > SH;
-        const float2 y0 = ys[hi ? Pf - kf : kf];
-        const float2 v = cmulc(hi ? cconj(y0) : y0, a.cf[kc]);
-        return k <= a.Kn ? v : make_float2(0.f, 0.f);
-    };
-    // input of the ring's half-length inverse transform at u: E + i O from the
-    // Hermitian part of Q~ (q1 = Q~_u, q2 = Q~_{Pn-u})
-    auto herm = [&](int u, float2 q1, float2 q2) {
-        const float2 zero = make_float2(0.f, 0.f);
-        const float2 av = u == 0 ? make_float2(q1.x, 0.f) : cscale(q1, 0.5f);
-        const float2 cv = u == 0 ? zero : cscale(cconj(q2), 0.5f);
-        const float2 E = cadd(av, cv);
-        const float2 O = cmulc(csub(av, cv), a.uw[u]);
-        return make_float2(E.x - O.y, E.y + O.x);
-    };
-    // item u < (Pn + 1)/2 writes slots u and Pn - u; item 0 writes slot 0 and,
-    // for even Pn, slot Pn/2 (one path for every lane: no branch on u, the
-    // loads of all rounds can be issued together)
-    constexpr int items = (Pn + 1) / 2;
-    if (act) {
-#pragma unroll
-        for (int i = 0; i < (items + T - 1) / T; ++i) {
-            const int u0 = lane + i * T;
-            const bool own = items % T == 0 || u0 < items;
-            const int u = min(u0, items - 1);
-            const int u2 = u == 0 ? ((Pn & 1) == 0 ? Pn / 2 : 0) : Pn - u;  // the second slot
-            const float2 qa = qmode(u), qb = qmode(u2);
-            const float2 ha = herm(u, qa, qb), hb = herm(u2, qb, u == 0 ? qb : qa);
-            if (own) {
-                buf[u] = ha;
-                if (u2 != 0) buf[u2] = hb;
-            }
-        }
-    }
-    __syncthreads();
-    cfft<Pn, true, cfft_wg_lanes(Pn, T)>(buf, a.ctwR, lane, lane < cfft_wg_lanes(Pn, T));
-    // q~(m): m = 2t -> Re z_t, m = 2t + 1 -> Im z_t;  F~_h(l) = (q~(l) + q~(l+Pn)) + i (q~(l) - q~(l+Pn)),
-    // stored in band order (the spread applies the conjugate half-pixel phase)
-    if (act) {
-#pragma unroll
-        for (int i = 0; i < RO; ++i) {
-            const int l0 = lane + i * T;
-            const int l = min(l0, Pn - 1);
-            const float2 z1 = buf[l >> 1];
-            const float av = (l & 1) ? z1.y : z1.x;
-            const int m = l + Pn;
-            const float2 z2 = buf[m >> 1];
-            const float cv = (m & 1) ? z2.y : z2.x;
-            const float2 Fh = make_float2(av + cv, av - cv);
-            if (Pn % T == 0 || l0 < Pn) Hb[slot[i]] = Fh;
-        }
-    }
-    __syncthreads();
-}
-
-template <int G, int W>
-__device__ __forceinline__ void ring_adj_spec_tile(const PlanDev& d, const WsLayout& L, char* wb, int n, float2* buf)
-{
-    const float* hT = (const float*)(wb + L.hdet);  // [nlam][D]
-    float2* Hb = (float2*)(wb + L.polar);
-    float2* syn = buf + d.npsi_max / 2;  // the synthesis transform after the ring buffer
-    constexpr int T = ring_spec_threads(G, W);
-    ring_adj_spec_head<T>(d, hT + (size_t)n * d.D, syn);
-    cfft_run_wg<false, G, T>(syn, d.fold_P >> 1, d.ctw + d.syn_ctw);
-    const RingSpecArgs a = ring_spec_args(d, n);
-    const int Pn = d.ring_off[n + 1] - a.off;
-    switch (Pn) {
-#define PAT_RING_ADJ_TAIL(LEN) \
-    case LEN: ring_adj_spec_tail<LEN, T>(d, a, syn, buf, Hb); break;
-        PAT_CFFT_LENGTHS_LO(PAT_RING_ADJ_TAIL)
-        default:
-            if constexpr (G >= 1) {
-                switch (Pn) {
-                    PAT_CFFT_LENGTHS_HI(PAT_RING_ADJ_TAIL)
-                    default:
-                        if constexpr (G >= 2) {
-                            switch (Pn) {
-                                PAT_CFFT_LENGTHS_HI2(PAT_RING_ADJ_TAIL)
-                                default: break;
-                            }
-                        }
-                        break;
-                }
-            }
-            break;
-#undef PAT_RING_ADJ_TAIL
     }
 }
 
@@ -2074,35 +1332,6 @@ __device__ __forceinline__ void colpass_adj_tile(const PlanDev& d, const WsLayou
         });
 }
 
-// ---------------------------------------------------------------------------
-// Launch wrappers.  Single-plan kernels: `batch` instances of one plan with
-// instance workspaces `wsp.stride` bytes apart.  Batch kernels (suffix _b):
-// one launch covers every instance of a heterogeneous batch; the workgroup's
-// work item is located in the per-stage prefix table and the instance's plan
-// is read from the device table.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ int batch_find(const int* __restrict__ base, int count, int item)
-{
-    int lo = 0, hi = count;  // base[lo] <= item < base[hi]
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (base[mid] <= item) lo = mid;
-        else hi = mid;
-    }
-    return lo;
-}
-
-// Locates the workgroup's instance and local tile for stage `st`; false for padding workgroups.
-__device__ __forceinline__ bool batch_item(const BatchDev& bt, int st, int& inst, int& tile)
-{
-    const int* base = bt.base + st * (bt.count + 1);
-    const int item = xcd_item(blockIdx.x, base[bt.count]);
-    if (item < 0) return false;
-    inst = batch_find(base, bt.count, item);
-    tile = item - base[inst];
-    return true;
-}
-
 __global__ __launch_bounds__(1024) void k_colpass_fwd(PlanDev d, WsLayout L, const float* __restrict__ f,
                                                      InstPtrs wsp, int NP)
 {
@@ -2166,100 +1395,6 @@ __global__ __launch_bounds__(kGatherThreads) void k_gather_b(BatchDev bt, char* 
     const PlanDev d = I.d;
     char* const wbs[1] = {ws + I.ws_off};
     gather_tile<1, CB>(d, I.L, wbs, 1, tile, I.gat_th, win);
-}
-
-// Ring kernels: at most kRingMaxThreads threads (one wave for most rings).  Both
-// are held to 128 VGPRs (four waves per SIMD), where the per-instance kernels
-// do not spill: they are latency bound, so resident waves count more than the
-// extra registers an unconstrained schedule would take.
-// Ring tile order: a ring's work grows with n, so the largest rings go first
-// and a launch ends on small ones.  The XCD ranges stay instance-major (an
-// instance's data in one L2).  RING_MAJOR (used when every XCD owns whole
-// instances, batch a multiple of 8): an XCD's tiles run ring-major across its
-// instances (largest ring of each instance, then the next); else instance by
-// instance.  Measured at 256^2, batch 64: the forward ring kernel is fastest
-// instance by instance (a ring's polar values follow the previous ring's), the
-// adjoint ring-major.
-template <bool RING_MAJOR>
-__device__ __forceinline__ bool ring_item(int w, int ntile, int batch, int& b, int& t)
-{
-    const int item = xcd_item(w, ntile * batch);
-    if (item < 0) return false;
-    if (RING_MAJOR && batch % kXcds == 0) {
-        const int per = batch / kXcds;  // instances per XCD
-        const int x = item / (per * ntile), q = item - x * per * ntile;
-        const int tr = q / per;
-        b = x * per + (q - tr * per);
-        t = ntile - 1 - tr;
-    } else {
-        b = item / ntile;
-        t = ntile - 1 - (item - b * ntile);
-    }
-    return true;
-}
-
-__global__ __launch_bounds__(kRingMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_fwd(PlanDev d, WsLayout L, InstPtrs wsp, int RT, int batch)
-{
-    extern __shared__ float2 sm[];
-    int b, t;
-    if (!ring_item<false>(blockIdx.x, (d.nlam + RT - 1) / RT, batch, b, t)) return;
-    ring_fwd_tile(d, L, wsp.ws + (size_t)b * wsp.stride, t, RT, sm);
-}
-
-__global__ __launch_bounds__(kRingMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_fwd_b(BatchDev bt, char* ws)
-{
-    extern __shared__ float2 sm[];
-    int i, tile;
-    if (!batch_item(bt, kStRing, i, tile)) return;
-    const BatchInst& I = bt.inst[i];
-    const PlanDev d = I.d;
-    if (d.ring_spec && d.ring_spec_grp == 2) ring_fwd_spec_tile<2, 1>(d, I.L, ws + I.ws_off, tile, sm);
-    else if (d.ring_spec) ring_fwd_spec_tile<1, 1>(d, I.L, ws + I.ws_off, tile, sm);
-    else ring_fwd_tile(d, I.L, ws + I.ws_off, tile, I.ring_rt, sm);
-}
-
-// Ring kernels of plans with compile-time transforms: one ring per workgroup
-// of ring_spec_threads(G, W) threads, largest rings first.  Length group G
-// (cfft.hpp): 0 up to kCfftSplit, 1 up to 1024 (one wave), 2 up to 2048 (two
-// waves); W waves per ring in the one-wave groups (the same arithmetic on
-// more lanes: small batches, where a ring's chain of phases is the critical
-// path).
-template <int G, int W>
-__global__ __launch_bounds__(ring_spec_threads(G, W)) void k_ring_fwd_spec(PlanDev d, WsLayout L, InstPtrs wsp, int batch)
-{
-    extern __shared__ float2 sm[];
-    int b, n;
-    if (!ring_item<false>(blockIdx.x, d.nlam, batch, b, n)) return;
-    ring_fwd_spec_tile<G, W>(d, L, wsp.ws + (size_t)b * wsp.stride, n, sm);
-}
-
-template <int G, int W>
-__global__ __launch_bounds__(ring_spec_threads(G, W)) void k_ring_adj_spec(PlanDev d, WsLayout L, InstPtrs wsp, int batch)
-{
-    extern __shared__ float2 sm[];
-    int b, n;
-    if (!ring_item<true>(blockIdx.x, d.nlam, batch, b, n)) return;
-    ring_adj_spec_tile<G, W>(d, L, wsp.ws + (size_t)b * wsp.stride, n, sm);
-}
-
-__global__ __launch_bounds__(kRingMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_adj(PlanDev d, WsLayout L, InstPtrs wsp, int RT, int batch)
-{
-    extern __shared__ float2 sm[];
-    int b, t;
-    if (!ring_item<true>(blockIdx.x, (d.nlam + RT - 1) / RT, batch, b, t)) return;
-    ring_adj_tile(d, L, wsp.ws + (size_t)b * wsp.stride, t, RT, sm);
-}
-
-__global__ __launch_bounds__(kRingMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_adj_b(BatchDev bt, char* ws)
-{
-    extern __shared__ float2 sm[];
-    int i, tile;
-    if (!batch_item(bt, kStRing, i, tile)) return;
-    const BatchInst& I = bt.inst[i];
-    const PlanDev d = I.d;
-    if (d.ring_spec && d.ring_spec_grp == 2) ring_adj_spec_tile<2, 1>(d, I.L, ws + I.ws_off, tile, sm);
-    else if (d.ring_spec) ring_adj_spec_tile<1, 1>(d, I.L, ws + I.ws_off, tile, sm);
-    else ring_adj_tile(d, I.L, ws + I.ws_off, tile, I.ring_rt, sm);
 }
 
 // Dense synthesis (explicit detector angles): `ntile` tiles per instance,

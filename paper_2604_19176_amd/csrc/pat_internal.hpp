@@ -329,6 +329,22 @@ struct pat_plan {
 };
 
 namespace pat {
+struct InstPtrs {
+    char* ws;         // workspace base of instance 0
+    size_t stride;    // bytes per instance
+};
+
+// Workgroups of a launch over `items` work items shared out over the XCDs
+// (xcd_item in device_util.hpp).
+constexpr int kXcds = 8;
+inline unsigned xcd_grid(int items) { return (unsigned)(((items + kXcds - 1) / kXcds) * kXcds); }
+
+// Launches of the ring kernels (ring_fwd.hip, ring_adj.hip).
+void ring_fwd_launch(const pat_plan* p, const InstPtrs& wsp, int batch, hipStream_t st);
+void ring_adj_launch(const pat_plan* p, const InstPtrs& wsp, int batch, hipStream_t st);
+void ring_fwd_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, hipStream_t st);
+void ring_adj_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, hipStream_t st);
+
 // Threads of a 2D-FFT pass workgroup over `nseq` sequences of the plan's grid side.
 int grid_threads(const pat_plan* p, int nseq);
 }  // namespace pat
