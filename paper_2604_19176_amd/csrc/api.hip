@@ -174,7 +174,14 @@ static int adjoint_run(const pat_plan* p, const float* g, float* f, int batch, v
     ring_adj_launch(p, wsp, batch, st);
     if ((rc = check_launch())) return rc;
     prof_mark(p, 1, 2 + qa, st);
-    {
+    if (d.spr_small) {
+        const int ib = tile_ib(c.spr_ib, batch);
+        const dim3 grid(xcd_grid(spread_small_tiles(d.Ng, d.NB) * ((batch + ib - 1) / ib))), blk(kSprWaves * 64);
+        const size_t lds = spread_small_lds(ib);
+        if (ib == 4) hipLaunchKernelGGL(k_spread_small<4>, grid, blk, lds, st, d, p->ws, wsp, batch);
+        else if (ib == 2) hipLaunchKernelGGL(k_spread_small<2>, grid, blk, lds, st, d, p->ws, wsp, batch);
+        else hipLaunchKernelGGL(k_spread_small<1>, grid, blk, lds, st, d, p->ws, wsp, batch);
+    } else {
         const int cb = c.spr_cb, ib = tile_ib(c.spr_ib, batch);
         const int items = ((d.Ng + cb - 1) / cb) * d.spr_rows * ((batch + ib - 1) / ib);
         const dim3 grid(xcd_grid(items));
@@ -547,7 +554,8 @@ static void batch_layout(pat_batch* b)
         items[kStDct] = I.n_pair_tiles;
         items[kStSynFwd] = d.syn_dense ? syn_fwd_tiles(d) : 0;
         items[kStSynAdj] = d.syn_dense ? syn_adj_tiles(d) : 0;
-        items[kStSpread] = ((d.Ng + b->spr_cb - 1) / b->spr_cb) * d.spr_rows;
+        items[kStSpread] = d.spr_small ? 0 : ((d.Ng + b->spr_cb - 1) / b->spr_cb) * d.spr_rows;
+        items[kStSpreadSmall] = d.spr_small ? spread_small_tiles(d.Ng, d.NB) : 0;
         for (int s = 0; s < kNumStages; ++s)
             b->base[(size_t)s * (n + 1) + i + 1] = b->base[(size_t)s * (n + 1) + i] + items[s];
         // workgroup sizes from the tile shapes copied into the instance (a later
@@ -730,7 +738,12 @@ extern "C" int pat_batch_adjoint(const pat_batch* b, const float* const* g_ptrs,
     }
     ring_adj_b_launch(bt, w, batch_items(b, kStRing), b->thr_ring, b->lds_ring, st);
     if ((rc = check_launch())) return rc;
-    {
+    if (batch_items(b, kStSpreadSmall) > 0) {
+        hipLaunchKernelGGL(k_spread_small_b, dim3(xcd_grid(batch_items(b, kStSpreadSmall))), dim3(kSprWaves * 64),
+                           spread_small_lds(1), st, bt, w);
+        if ((rc = check_launch())) return rc;
+    }
+    if (batch_items(b, kStSpread) > 0) {
         const dim3 grid(xcd_grid(batch_items(b, kStSpread)));
         const size_t lds = spread_lds(b->spr_cb, 1);
         switch (b->spr_cb) {

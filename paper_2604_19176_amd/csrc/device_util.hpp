@@ -20,8 +20,8 @@ __device__ __forceinline__ int xcd_item(int w, int U)
 }
 
 // The 8 taps of the ES kernel phi(t) = exp(beta (sqrt(1 - (2t/w)^2) - 1)) at
-// t = frac + 3 - d (d = 0..7, frac in [0, 1)): z = t / 4 lies in [-1, 1], so
-// 1 - z^2 only needs a clamp against rounding below 0; the hardware square
+// t = frac + 3 - d (d = 0..7, frac in [0, 1]): z = t / 4 lies in [-1, 1] also
+// when rounded, so 1 - z^2, rounded once, is never negative; the hardware square
 // root and base-2 exponential (about 1 ulp each) are used directly, since the
 // argument of the exponential lies in [-beta log2(e), 0].  The same routine
 // serves the interpolation and the spread, which keeps them exact transposes.
@@ -32,8 +32,7 @@ __device__ __forceinline__ void es_weights8(float frac, float (&w)[8])
 #pragma unroll
     for (int d = 0; d < 8; ++d) {
         const float z = z0 + 0.25f * (float)(3 - d);
-        const float q = fmaxf(fmaf(-z, z, 1.0f), 0.0f);
-        w[d] = __builtin_amdgcn_exp2f(fmaf(kb, __builtin_amdgcn_sqrtf(q), -kb));
+        w[d] = __builtin_amdgcn_exp2f(fmaf(kb, __builtin_amdgcn_sqrtf(fmaf(-z, z, 1.0f)), -kb));
     }
 }
 

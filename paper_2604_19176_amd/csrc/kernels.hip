@@ -1145,6 +1145,189 @@ __device__ __forceinline__ void spread_tile(const PlanDev& d, const WsLayout& L,
 }
 
 // ---------------------------------------------------------------------------
+// adjoint: the spread of small launches (plans with spr_small), on the matrix
+// cores.  A point of band r0 (footprint base row) adds wy[dy] wx[dx] h to the
+// 8 x 8 cells at rows r0 + dy and columns bx + dx, so over a band 16 columns
+// and the band's 8 rows take the product
+//   out[(dy, re/im)][column] = sum_p (wy[p][dy] h[p].re/im) wx[p][column],
+// a 16 x 16 output with the points as the contraction (v_mfma_f32_16x16x4f32,
+// four points at a time; wx is zero outside a point's footprint).
+//
+// A workgroup owns a row tile (kSpreadTh bands) x 16 columns, each of its
+// kSprWaves waves kSprBands of the bands.  A wave stages up to 64 points at a time
+// in LDS, one per lane (16 ES weights, the value times the conjugate half-pixel
+// phase), the next points' loads in flight.  Accumulator rows are used
+// cyclically (row r in slot r mod 8): a finished row leaves its slot to the row
+// eight further on.  At the end the waves' parts are added in wave order in LDS;
+// the rows go where the row tile's go in spread_tile (grid and tail region), and
+// every sum has a fixed order, the same for every launch shape and batch.
+//
+// Bound by the latency of a wave's chain (CSR bounds, points, staging, matrix
+// instructions): 16 columns x 2 bands per wave give 16 times as many, 8 times
+// shorter chains as one lane per column x 8 bands.  For large launches the
+// lane-per-column form does less work: a point's 8 columns fill about a third
+// of the matrix operand, and float32 matrix and vector instructions share the
+// SIMD's issue.  256^2, one image: 12 us against 22; 32^2: 8.4 against 29.  1024^2,
+// batch 8: 263 against 212.
+// ---------------------------------------------------------------------------
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Orders a wave's LDS writes before its later reads by other lanes (LDS
+// operations of a wave complete in order; this keeps the compiler's order).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+static_assert(kSprBands == 2, "a wave's first row is done after its first band");
+
+template <int IB>
+__device__ __forceinline__ void spread_small_tile(const PlanDev& d, const WsLayout& L, char* wb0, size_t stride, int nb,
+                                                  int tile, float* lds)
+{
+    constexpr int NR = kSprBands + 7;  // grid rows a wave's bands reach
+    const int Ng = d.Ng, NB = d.NB;
+    const int ncg = (Ng + kSprCols - 1) / kSprCols;
+    const int rt = tile / ncg, C0 = (tile - rt * ncg) * kSprCols;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n16 = lane & 15, kq = lane >> 4;
+    float* wls = lds + w * spread_wave_words(IB);
+    float* swx = wls;                               // [64][kSprWx]: the 8 x weights, then a zero
+    float* swy = swx + 64 * kSprWx;                 // [64][8]
+    float* sh = swy + 64 * 8;                       // [64][re, im][IB]
+    int* sbx = (int*)(sh + 64 * 2 * IB);            // [64] footprint column, relative to the tile
+    const float2* H[IB];
+#pragma unroll
+    for (int b = 0; b < IB; ++b) H[b] = (const float2*)(wb0 + (size_t)min(b, nb - 1) * stride + L.polar);
+    // the bands' points as one list: footprint columns C0 - 7 .. C0 + 15, the
+    // wrapped ones (columns Ng - 7 .. Ng - 1 seen from the tile at column 0)
+    // first; each band's part is padded to whole groups of four
+    int ra[kSprBands], na[kSprBands], rb[kSprBands], n[kSprBands], at[kSprBands + 1];
+    at[0] = 0;
+#pragma unroll
+    for (int q = 0; q < kSprBands; ++q) {
+        const int band = rt * kSpreadTh + w * kSprBands + q;
+        const bool ok = band < NB;
+        const int* bp = d.band_ptr + (size_t)min(band, NB - 1) * (Ng + 1);
+        rb[q] = bp[max(C0 - 7, 0)];
+        const int n2 = bp[min(C0 + kSprCols, Ng)] - rb[q];
+        ra[q] = C0 == 0 ? bp[Ng - 7] : 0;
+        na[q] = ok && C0 == 0 ? bp[Ng] - ra[q] : 0;
+        n[q] = ok ? na[q] + n2 : 0;
+        at[q + 1] = at[q] + ((n[q] + 3) & ~3);
+    }
+    const int tot = at[kSprBands];
+    f32x4 acc[IB];
+    float2 done[IB];  // the wave's first row, complete after its first band (lanes kq = 0)
+#pragma unroll
+    for (int b = 0; b < IB; ++b) {
+        acc[b] = (f32x4)(0.f);
+        done[b] = make_float2(0.f, 0.f);
+    }
+    swx[lane * kSprWx + 8] = 0.f;
+    // a lane's point: entry e of the list (past a band's points: a zero value)
+    float4 gq;
+    float2 ph, h[IB];
+    int bxr;
+    auto fetch = [&](int e) {
+        const int q = e >= at[1];
+        const int i = e - (q ? at[1] : 0), na_ = q ? na[1] : na[0];
+        const bool ok = i < (q ? n[1] : n[0]);
+        const int sl = ok ? (i < na_ ? (q ? ra[1] : ra[0]) + i : (q ? rb[1] : rb[0]) + (i - na_)) : 0;
+        gq = d.bpt_geo[sl];
+        ph = d.bpt_phase[sl];
+#pragma unroll
+        for (int b = 0; b < IB; ++b) {
+            const float2 v = H[b][sl];
+            h[b] = ok ? v : make_float2(0.f, 0.f);
+        }
+        bxr = (i < na_ ? Ng : 0) + C0;
+    };
+    auto stage = [&]() {
+        float wv[8];
+        es_weights8(gq.z, wv);
+        float4* px = (float4*)(swx + lane * kSprWx);
+        px[0] = make_float4(wv[0], wv[1], wv[2], wv[3]);
+        px[1] = make_float4(wv[4], wv[5], wv[6], wv[7]);
+        es_weights8(gq.w, wv);
+        float4* py = (float4*)(swy + lane * 8);
+        py[0] = make_float4(wv[0], wv[1], wv[2], wv[3]);
+        py[1] = make_float4(wv[4], wv[5], wv[6], wv[7]);
+        sbx[lane] = fbits(gq.x) - bxr;
+        // explicit roundings: the same product for every IB
+#pragma unroll
+        for (int b = 0; b < IB; ++b) {
+            sh[(lane * 2) * IB + b] = fmaf(h[b].x, ph.x, __fmul_rn(h[b].y, ph.y));
+            sh[(lane * 2 + 1) * IB + b] = fmaf(h[b].y, ph.x, -__fmul_rn(h[b].x, ph.y));
+        }
+    };
+    // the staged points p0 .. p1 - 1 (whole groups of four) of a band; dy: the tap of the lane's row
+    auto feed = [&](int p0, int p1, int dy) {
+        for (int c = p0; c < p1; c += 4) {
+            const int p = c + kq;
+            const float wx = swx[p * kSprWx + (int)min((unsigned)(n16 - sbx[p]), 8u)], wy = swy[p * 8 + dy];
+            const float* hp = sh + (p * 2 + (n16 & 1)) * IB;
+#pragma unroll
+            for (int b = 0; b < IB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wy * hp[b], wx, acc[b], 0, 0, 0);
+        }
+    };
+    if (tot > 0) fetch(lane);
+    bool second = false;
+    for (int base = 0; base < tot; base += 64) {
+        const int bend = min(base + 64, tot);
+        stage();
+        wave_lds_fence();
+        if (base + 64 < tot) fetch(base + 64 + lane);
+        const int mid = min(max(at[1], base), bend);
+        feed(0, mid - base, n16 >> 1);
+        if (!second && at[1] <= bend) {
+            second = true;
+#pragma unroll
+            for (int b = 0; b < IB; ++b) {
+                done[b] = make_float2(acc[b][0], acc[b][1]);
+                if (kq == 0) acc[b][0] = acc[b][1] = 0.f;
+            }
+        }
+        feed(mid - base, bend - base, ((n16 >> 1) - 1) & 7);
+        wave_lds_fence();
+    }
+    // the wave's rows to LDS [IB][NR][16] (its staging area is free), then their sum over the waves
+    float2* ob = (float2*)wls;
+#pragma unroll
+    for (int b = 0; b < IB; ++b) {
+        if (kq == 0) ob[b * NR * kSprCols + n16] = done[b];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const int slot = 2 * kq + r;  // slot 0 holds row 8
+            ob[(b * NR + (slot ? slot : 8)) * kSprCols + n16] = make_float2(acc[b][2 * r], acc[b][2 * r + 1]);
+        }
+    }
+    __syncthreads();
+    constexpr int ROWS = kSpreadTh + 7;
+    const bool last = (rt + 1) * kSpreadTh >= NB;
+    for (int t = threadIdx.x; t < nb * ROWS * kSprCols; t += kSprWaves * 64) {
+        const int b = t / (ROWS * kSprCols), e = t - b * (ROWS * kSprCols), row = e / kSprCols, col = e % kSprCols;
+        float2 sum = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int v = 0; v < kSprWaves; ++v) {
+            const int r = row - v * kSprBands;
+            const float2* src = (const float2*)(lds + v * spread_wave_words(IB));
+            const float2 x = src[(b * NR + min(max(r, 0), NR - 1)) * kSprCols + col];
+            if (r >= 0 && r < NR) sum = cadd(sum, x);
+        }
+        const int gr = rt * kSpreadTh + row;
+        if (C0 + col >= Ng) continue;
+        char* wb = wb0 + (size_t)b * stride;
+        if (row < kSpreadTh || last) {
+            if (gr < d.Hy) ((float2*)(wb + L.grid))[(size_t)gr * Ng + C0 + col] = sum;
+        } else {
+            ((float2*)(wb + L.tail))[((size_t)rt * 7 + row - kSpreadTh) * Ng + C0 + col] = sum;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // adjoint: row pass (inverse FFT along x, crop to the N image columns)
 // ---------------------------------------------------------------------------
 // Grid row r = 8 q + k takes row tile q's part (its grid row, or, if the tile
@@ -1504,6 +1687,29 @@ __global__ __launch_bounds__(CB) __attribute__((amdgpu_waves_per_eu(IB == 4 ? 3 
 #pragma unroll
     for (int b = 0; b < IB; ++b) wbs[b] = wsp.ws + (size_t)(b0 + (b < nb ? b : 0)) * wsp.stride;
     spread_tile<IB, CB>(d, L, wbs, nb, item - g * per, sf);
+}
+
+template <int IB>
+__global__ __launch_bounds__(kSprWaves * 64) void k_spread_small(PlanDev d, WsLayout L, InstPtrs wsp, int batch)
+{
+    extern __shared__ __align__(16) float sfs[];
+    const int per = spread_small_tiles(d.Ng, d.NB);
+    const int ngroups = (batch + IB - 1) / IB;
+    const int item = xcd_item(blockIdx.x, per * ngroups);
+    if (item < 0) return;
+    const int g = item / per;
+    const int b0 = g * IB, nb = min(IB, batch - b0);
+    spread_small_tile<IB>(d, L, wsp.ws + (size_t)b0 * wsp.stride, wsp.stride, nb, item - g * per, sfs);
+}
+
+__global__ __launch_bounds__(kSprWaves * 64) void k_spread_small_b(BatchDev bt, char* ws)
+{
+    extern __shared__ __align__(16) float sfs[];
+    int i, tile;
+    if (!batch_item(bt, kStSpreadSmall, i, tile)) return;
+    const BatchInst& I = bt.inst[i];
+    const PlanDev d = I.d;
+    spread_small_tile<1>(d, I.L, ws + I.ws_off, 0, 1, tile, sfs);
 }
 
 template <int CB>

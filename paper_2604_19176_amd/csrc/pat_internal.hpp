@@ -116,6 +116,7 @@ struct PlanDev {
     // per row tile t (and zero for every t the adjoint row pass can name past
     // the last): (first slab row of run 0) << 4 | log2 S, or 0 if swept whole
     const unsigned* spr_head;
+    int spr_small;          // 1: the spread of small launches (kSprSmallMax); no tile is split
     // synthesis over detector angles theta_d = theta_0 + d dtheta
     int fold_P;             // P if dtheta = 2 pi s / P (P = 2^a3^b, gcd(s, P) = 1): fold k mod P, one FFT; else 0
     int fold_s;             // s: detector d is point s d of the P-point angular grid (s (D - 1) < P)
@@ -182,6 +183,22 @@ __host__ __device__ constexpr size_t spread_lds_words(int CAP, int IB)
     return (size_t)CAP * (17 + 2 * IB) + 3 * (size_t)(CAP / 2 + 10);
 }
 
+// The spread of small launches: tiles of one row tile x kSprCols columns, kSprWaves
+// waves of kSprBands bands each; a wave's LDS holds 64 staged points (kSprWx words
+// for the 8 x weights and a zero, 8 y weights, IB complex values, the footprint
+// column), then its output rows [IB][kSprBands + 7][kSprCols] complex.
+constexpr int kSprCols = 16;
+constexpr int kSprWaves = 4;
+constexpr int kSprBands = 2;
+constexpr int kSprWx = 12;
+__host__ __device__ constexpr int spread_wave_words(int IB) { return 64 * (kSprWx + 8 + 2 * IB + 1); }
+__host__ __device__ constexpr size_t spread_small_lds(int IB) { return sizeof(float) * (size_t)kSprWaves * spread_wave_words(IB); }
+static_assert(spread_wave_words(1) >= 2 * (kSprBands + 7) * kSprCols &&
+              spread_wave_words(4) >= 4 * 2 * (kSprBands + 7) * kSprCols, "a wave's output rows fit its staging area");
+// Plans whose largest call spreads at most this many points take it; above, the
+// chip is full either way and the lane-per-column form does less work per point.
+constexpr long kSprSmallMax = 3L << 20;
+
 // Ring kernels: a ring workgroup has at least (K + 1) / kRingModesPerThread
 // threads; its fills of ring inputs issue kRingFillUnroll loads per thread
 // and input at a time (more would cost the transforms registers).
@@ -232,6 +249,11 @@ inline bool gather_shape_ok(int cb, int th, int ib)
 // the order is still the same for every launch shape and batch.
 constexpr int kSpreadTh = 8;
 __host__ __device__ inline int spread_row_tiles(int NB) { return (NB + kSpreadTh - 1) / kSpreadTh; }
+static_assert(kSpreadTh == kSprWaves * kSprBands, "the small launches' waves share a row tile");
+__host__ __device__ inline int spread_small_tiles(int Ng, int NB)
+{
+    return ((Ng + kSprCols - 1) / kSprCols) * spread_row_tiles(NB);
+}
 // slab rows of one run of a row tile split into S runs
 __host__ __device__ inline int spread_run_rows(int S) { return kSpreadTh / S + 7; }
 inline bool spread_shape_ok(int cb, int th, int ib)
@@ -269,6 +291,7 @@ enum BatchStage {
     kStRing,      // ring kernels: ceil(nlam / ring_rt) tiles
     kStDct,       // cosine transforms: ceil(ceil(D / 2) / dct_dp) tiles
     kStSpread,    // spread: ceil(Ng / spr_cb) x spr_rows tiles
+    kStSpreadSmall,  // spread of plans with spr_small: spread_small_tiles (they have no kStSpread items)
     kStSynFwd,    // dense synthesis (explicit angles): ceil(nlam / 64) x ceil(D / 64) tiles, else 0
     kStSynAdj,    // its transpose: ceil(nlam / 64) x ceil(2 (K + 1) / 64) tiles, else 0
     kNumStages

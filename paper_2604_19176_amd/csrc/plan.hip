@@ -633,25 +633,18 @@ extern "C" int pat_bessel_jn_table(int kmax, double x, double* out)
 
 // Spread work rows.  In band rb the lane of column c visits the points whose
 // footprint base column is c - 7 .. c (mod Ng); a row tile's longest lane,
-// summed over its bands, bounds its workgroup's time.  For batches: a row tile
+// summed over its bands, bounds its workgroup's time.  A row tile
 // among the first kSpreadSplitTiles whose longest lane exceeds
 // kSpreadSplitFactor times the median over the row tiles is split into the
 // fewest runs S (2 or kSpreadMaxRuns) that bring every run's longest lane
-// under that limit, or into kSpreadMaxRuns.  Plans for single instances
-// (max_batch 1), whose spread is one wave per tile and bound by each tile's
-// chain of bands, split every row tile whose longest lane exceeds
-// kSpreadSplitFactorSingle times the median: more, shorter work rows, at the
-// cost of the slab rows the adjoint row pass adds up, unless those would
-// exceed kSpreadSlabCapSingle bytes per instance (then the batched rule).  The last row tile,
+// under that limit, or into kSpreadMaxRuns.  The last row tile,
 // which writes the grid's final rows itself, is never split.  Output: the work
 // rows (first band, last band, first slab row or -1, row tile), per row tile
 // (S, first slab row), and the slab rows in all.  The split is a property of
 // the plan: every launch shape and batch size of a plan sums in its order.
 constexpr double kSpreadSplitFactor = 1.5;
-constexpr double kSpreadSplitFactorSingle = 0.7;
-constexpr size_t kSpreadSlabCapSingle = 32u << 20;  // slab bytes per instance of a single-instance plan
 
-static void spread_runs(const std::vector<int>& bptr, int NB, int Ng, bool single, std::vector<int4>& rows,
+static void spread_runs(const std::vector<int>& bptr, int NB, int Ng, std::vector<int4>& rows,
                         std::vector<int2>& split, int& slab_rows)
 {
     const int nrt = spread_row_tiles(NB);
@@ -682,23 +675,13 @@ static void spread_runs(const std::vector<int>& bptr, int NB, int Ng, bool singl
     for (int t = 0; t < nrt; ++t) whole[t] = longest(t, 1);
     std::vector<int> srt(whole);
     std::sort(srt.begin(), srt.end());
-    const double limit = (single ? kSpreadSplitFactorSingle : kSpreadSplitFactor) * srt[srt.size() / 2];
+    const double limit = kSpreadSplitFactor * srt[srt.size() / 2];
     // runs per row tile
     std::vector<int> runs(nrt, 1);
-    long used = 0;  // slab rows
-    for (int t = 0; t + 1 < nrt; ++t) {
-        if (!single && t >= kSpreadSplitTiles) break;
+    for (int t = 0; t + 1 < nrt && t < kSpreadSplitTiles; ++t) {
         int S = 1;
         while (S < kSpreadMaxRuns && longest(t, S) > limit) S *= 2;
         runs[t] = S;
-        if (S > 1) used += (long)S * spread_run_rows(S);
-    }
-    // a single-instance plan whose slab would exceed kSpreadSlabCapSingle
-    // bytes per instance takes the batched rule instead (splitting only part
-    // of the tiles leaves the unsplit ones as the longest chains)
-    if (single && used * (long)((size_t)Ng * sizeof(float2)) > (long)kSpreadSlabCapSingle) {
-        spread_runs(bptr, NB, Ng, false, rows, split, slab_rows);
-        return;
     }
     rows.clear();
     split.assign(nrt, make_int2(1, -1));
@@ -965,7 +948,14 @@ static int build_tables(const pat_plan_desc* desc, const Derived& dv, pat_plan* 
     }
     std::vector<int4> sprRow;
     std::vector<int2> sprSplit;
-    spread_runs(bptr, NB, Ng, desc->max_batch == 1, sprRow, sprSplit, d.slab_rows);
+    d.spr_small = (long)npts * desc->max_batch <= kSprSmallMax;
+    d.slab_rows = 0;
+    if (d.spr_small) {  // no work rows, no tile split
+        sprRow.push_back(make_int4(0, 0, -1, 0));
+        sprSplit.assign(spread_row_tiles(NB), make_int2(1, -1));
+    } else {
+        spread_runs(bptr, NB, Ng, sprRow, sprSplit, d.slab_rows);
+    }
     d.spr_rows = (int)sprRow.size();
     // the adjoint row pass looks up row tiles r / 8 and r / 8 - 1 of its grid rows r < Hy
     std::vector<unsigned> sprHead((size_t)(d.Hy + 7) / 8 + 1, 0u);
