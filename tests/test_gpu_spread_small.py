@@ -13,6 +13,13 @@ from pat_inputs import Geometry
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
 # Ng = 32, 36, 54, 108: 2, 2.25, 3.4 and 6.75 column tiles; NB = Ng / 2 + 2 bands = 18, 20, 29, 56
 @pytest.mark.parametrize("n", [16, 18, 26, 50])
 @pytest.mark.parametrize("batch", [1, 3, 5])
