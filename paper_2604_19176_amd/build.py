@@ -10,8 +10,9 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpat.so")
-SOURCES = ["ring_adj.hip", "ring_fwd.hip", "api.hip", "plan.hip", "tune.hip", "sim.hip"]
-HEADERS = ["pat_internal.hpp", "device_util.hpp", "fft.hpp", "cfft.hpp", "ring.hpp", "kernels.hip"]
+SOURCES = ["ring_adj.hip", "ring_fwd.hip", "grid_adj.hip", "grid_fwd.hip", "api.hip", "plan.hip", "tune.hip", "sim.hip"]
+HEADERS = ["pat_internal.hpp", "device_util.hpp", "fft.hpp", "cfft.hpp", "grid.hpp", "ring.hpp",
+           "kernels.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

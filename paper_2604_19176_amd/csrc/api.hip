@@ -116,12 +116,10 @@ static int forward_run(const pat_plan* p, const float* f, float* g, int batch, v
     const LaunchCfg& c = p->cfg;
     const InstPtrs wsp{(char*)ws, p->ws.bytes};
     prof_mark(p, 0, 0, st);
-    hipLaunchKernelGGL(k_colpass_fwd, dim3(p->n_col_tiles, batch), dim3(p->thr_col), fft_tile_lds(c.col_np, p->h_fft_grid), st,
-                       d, p->ws, f, wsp, c.col_np);
+    colpass_fwd_launch(p, f, wsp, batch, st);
     if ((rc = check_launch())) return rc;
     prof_mark(p, 0, 1, st);
-    hipLaunchKernelGGL(k_rowpass_fwd, dim3((d.Hy + c.row_rpb - 1) / c.row_rpb, batch), dim3(p->thr_row),
-                       fft_tile_lds(c.row_rpb, p->h_fft_grid), st, d, p->ws, wsp, c.row_rpb);
+    rowpass_fwd_launch(p, wsp, batch, st);
     if ((rc = check_launch())) return rc;
     prof_mark(p, 0, 2, st);
     {
@@ -192,12 +190,10 @@ static int adjoint_run(const pat_plan* p, const float* g, float* f, int batch, v
     }
     if ((rc = check_launch())) return rc;
     prof_mark(p, 1, 3 + qa, st);
-    hipLaunchKernelGGL(k_rowpass_adj, dim3((d.Hy + c.row_rpb - 1) / c.row_rpb, batch), dim3(p->thr_row),
-                       fft_tile_lds(c.row_rpb, p->h_fft_grid), st, d, p->ws, wsp, c.row_rpb);
+    rowpass_adj_launch(p, wsp, batch, st);
     if ((rc = check_launch())) return rc;
     prof_mark(p, 1, 4 + qa, st);
-    hipLaunchKernelGGL(k_colpass_adj, dim3(p->n_col_tiles, batch), dim3(p->thr_col), fft_tile_lds(c.col_np, p->h_fft_grid), st,
-                       d, p->ws, wsp, f, c.col_np, d.D);
+    colpass_adj_launch(p, wsp, f, batch, st);
     if ((rc = check_launch())) return rc;
     prof_mark(p, 1, 5 + qa, st);
     return PAT_OK;
@@ -560,13 +556,14 @@ static void batch_layout(pat_batch* b)
             b->base[(size_t)s * (n + 1) + i + 1] = b->base[(size_t)s * (n + 1) + i] + items[s];
         // workgroup sizes from the tile shapes copied into the instance (a later
         // set_launch or autotune of the plan does not change this batch)
-        b->thr_col = std::max<unsigned>(b->thr_col, grid_threads(p, I.col_np));
-        b->thr_row = std::max<unsigned>(b->thr_row, grid_threads(p, I.row_rpb));
+        b->thr_col = std::max(b->thr_col, I.thr_col);
+        b->thr_row = std::max(b->thr_row, I.thr_row);
+        b->grid_hi = b->grid_hi || (d.grid_spec && d.Ng > 1024);
         b->thr_ring = std::max<unsigned>(b->thr_ring, p->thr_ring);
         b->thr_dct = std::max<unsigned>(b->thr_dct, d.dct_spec ? I.dct_dp * cfft_lanes(2 * d.M)
                                                                : fft_workgroup_threads(I.dct_dp, p->h_fft_dct));
-        b->lds_col = std::max(b->lds_col, fft_tile_lds(I.col_np, p->h_fft_grid));
-        b->lds_row = std::max(b->lds_row, fft_tile_lds(I.row_rpb, p->h_fft_grid));
+        b->lds_col = std::max(b->lds_col, I.lds_col);
+        b->lds_row = std::max(b->lds_row, I.lds_row);
         b->lds_ring = std::max(b->lds_ring, p->lds_ring);
         b->lds_dct = std::max(b->lds_dct, dct_tile_lds(p, I.dct_dp));
     }
@@ -615,8 +612,12 @@ extern "C" int pat_batch_create(pat_plan* const* plans, int count, pat_batch** o
         I.L = p->ws;
         I.ws_off = off;
         off += (p->ws.bytes + 255) & ~(size_t)255;
-        I.col_np = p->cfg.col_np;
-        I.row_rpb = p->cfg.row_rpb;
+        I.col_np = p->np_col;
+        I.row_rpb = p->np_row;
+        I.thr_col = p->thr_col;
+        I.thr_row = p->thr_row;
+        I.lds_col = p->lds_col;
+        I.lds_row = p->lds_row;
         I.ring_rt = p->cfg.ring_rt;
         I.dct_dp = p->cfg.dct_dp;
         I.n_col_tiles = p->n_col_tiles;
@@ -691,11 +692,9 @@ extern "C" int pat_batch_forward(const pat_batch* b, const float* const* f_ptrs,
     hipStream_t st = (hipStream_t)stream;
     const BatchDev bt = batch_dev(b);
     char* w = (char*)ws;
-    hipLaunchKernelGGL(k_colpass_fwd_b, dim3(xcd_grid(batch_items(b, kStCol))), dim3(b->thr_col), b->lds_col, st, bt,
-                       f_ptrs, w);
+    colpass_fwd_b_launch(bt, f_ptrs, w, batch_items(b, kStCol), b->thr_col, b->lds_col, b->grid_hi, st);
     if ((rc = check_launch())) return rc;
-    hipLaunchKernelGGL(k_rowpass_fwd_b, dim3(xcd_grid(batch_items(b, kStRow))), dim3(b->thr_row), b->lds_row, st, bt,
-                       w);
+    rowpass_fwd_b_launch(bt, w, batch_items(b, kStRow), b->thr_row, b->lds_row, b->grid_hi, st);
     if ((rc = check_launch())) return rc;
     {
         const dim3 grid(xcd_grid(batch_items(b, kStGather))), blk(kGatherThreads);
@@ -754,10 +753,8 @@ extern "C" int pat_batch_adjoint(const pat_batch* b, const float* const* g_ptrs,
         }
     }
     if ((rc = check_launch())) return rc;
-    hipLaunchKernelGGL(k_rowpass_adj_b, dim3(xcd_grid(batch_items(b, kStRow))), dim3(b->thr_row), b->lds_row, st, bt,
-                       w);
+    rowpass_adj_b_launch(bt, w, batch_items(b, kStRow), b->thr_row, b->lds_row, b->grid_hi, st);
     if ((rc = check_launch())) return rc;
-    hipLaunchKernelGGL(k_colpass_adj_b, dim3(xcd_grid(batch_items(b, kStCol))), dim3(b->thr_col), b->lds_col, st, bt,
-                       w, f_ptrs);
+    colpass_adj_b_launch(bt, w, f_ptrs, batch_items(b, kStCol), b->thr_col, b->lds_col, b->grid_hi, st);
     return check_launch();
 }

@@ -126,12 +126,24 @@ constexpr int kCfftSplit = 512;
 // 1: up to 1024, 2: up to 2048), W waves per ring in the one-wave groups
 __host__ __device__ constexpr int ring_spec_threads(int G, int W = 1) { return G == 2 ? 2 * kCfftLanes : W * kCfftLanes; }
 
-// Grid sides Ng with a compile-time transform (2D-FFT passes)
-#define PAT_GRID_LENGTHS(X) X(128) X(256) X(512) X(1024) X(2048)
+// The column passes' sums of a column: over a sequence's lanes in kColSumGroups
+// groups, then over the groups, one order for every tile shape.
+constexpr int kColSumGroups = 8;
+
+// Grid sides Ng with a compile-time transform (2D-FFT passes, grid.hpp): every
+// even 2^a 3^b from 32 to 2048, in two groups (one wave per sequence, two waves)
+#define PAT_GRID_LENGTHS_LO(X)                                                                                 \
+    X(32) X(36) X(48) X(54) X(64) X(72) X(96) X(108) X(128) X(144) X(162) X(192) X(216) X(256) X(288) X(324) \
+    X(384) X(432) X(486) X(512) X(576) X(648) X(768) X(864) X(972) X(1024)
+#define PAT_GRID_LENGTHS_HI(X) X(1152) X(1296) X(1458) X(1536) X(1728) X(1944) X(2048)
+#define PAT_GRID_LENGTHS(X) PAT_GRID_LENGTHS_LO(X) PAT_GRID_LENGTHS_HI(X)
 
 __host__ __device__ constexpr bool grid_len_ok(int n)
 {
-    return n == 128 || n == 256 || n == 512 || n == 1024 || n == 2048;
+#define PAT_GRID_CASE_OK(L) if (n == L) return true;
+    PAT_GRID_LENGTHS(PAT_GRID_CASE_OK)
+#undef PAT_GRID_CASE_OK
+    return false;
 }
 
 __host__ __device__ constexpr bool cfft_len_ok(int n)
@@ -171,6 +183,10 @@ __device__ __forceinline__ constexpr int cfft_slot(int i)
     return PAD ? i + (i >> 4) : i;
 }
 __host__ __device__ constexpr int cfft_padded_len(int n) { return n + n / 16; }
+// Stride of the column passes' sequences in LDS: neighbouring threads work on
+// neighbouring sequences, which a stride of 4 modulo 32 values keeps on
+// different banks.
+__host__ __device__ constexpr int grid_col_ld(int n) { return (cfft_padded_len(n) + 27) / 32 * 32 + 4; }
 
 // The twiddles of one pass for a lane's RND butterflies: w^{r k}, r = 1..R-1,
 // k = j mod NS (empty for the pass with NS = 1).
@@ -279,6 +295,118 @@ __device__ __forceinline__ void cfft_passes(float2* x, const float2* __restrict_
         pass_tw_load<N, P.rad[S], P.ns[S], P.twoff[S], T>(cur, tw, active, lane);
         cfft_passes_tw<N, INV, S, PAD, T>(x, tw, active, lane, cur);
     }
+}
+
+// A transform whose first pass takes its inputs from the caller and whose last
+// pass hands its outputs to the caller, so that memory is read and written
+// without a copy in LDS: `load(v)` fills v[i][r] with the inputs at positions
+// cfft_first<N, T>::pos(lane, i, r), `out(pos, value)` takes each output.  x: the
+// sequence's LDS (padded layout, cfft_padded_len(N) slots).  Sync orders the
+// LDS accesses of the sequence's lanes: SyncWg a workgroup barrier (every
+// thread calls), SyncWave a wave's own order (T = 64, waves independent).
+// OUT_LDS: out writes the sequence's LDS (the call orders it before and after).
+struct SyncWg {
+    __device__ static __forceinline__ void sync() { __syncthreads(); }
+};
+struct SyncWave {
+    // LDS operations of a wave complete in order; this keeps the compiler's order
+    __device__ static __forceinline__ void sync()
+    {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+};
+
+template <int N, int T>
+struct cfft_first {
+    static constexpr int R = CPlanOf<N>::p.rad[0], NB = N / R, RND = (NB + T - 1) / T;
+    // butterfly i of the lane is its own (the last round's idle lanes repeat the last butterfly)
+    __device__ static __forceinline__ bool own(int lane, int i) { return NB % T == 0 || i + 1 < RND || lane + i * T < NB; }
+    __device__ static __forceinline__ int pos(int lane, int i, int r)
+    {
+        const int j = lane + i * T;
+        return ((NB % T == 0 || i + 1 < RND) ? j : min(j, NB - 1)) + r * NB;
+    }
+};
+
+template <int N, bool INV, int S, int T, class Sync, bool OUT_LDS, class Out>
+__device__ __forceinline__ void cfft_stream_passes(float2* __restrict__ x, const float2* __restrict__ tw, bool active,
+                                                   int lane, const PassTw<N, CPlanOf<N>::p.rad[S], CPlanOf<N>::p.ns[S], T>& cur,
+                                                   Out out)
+{
+    constexpr CPlan P = CPlanOf<N>::p;
+    constexpr int R = P.rad[S], NS = P.ns[S], NB = N / R, RND = (NB + T - 1) / T;
+    float2 v[RND][R];
+    if (active) {
+#pragma unroll
+        for (int i = 0; i < RND; ++i) {
+            const int j0 = lane + i * T;
+            const int j = (NB % T == 0 || i + 1 < RND) ? j0 : min(j0, NB - 1);
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[i][r] = x[cfft_slot<true>(j + r * NB)];
+#pragma unroll
+            for (int r = 1; r < R; ++r)
+                v[i][r] = INV ? cmulc(v[i][r], cur.w[i][r - 1]) : cmul(v[i][r], cur.w[i][r - 1]);
+            butterfly<R, INV>(v[i]);
+        }
+    }
+    if constexpr (S + 1 < P.np) {
+        PassTw<N, P.rad[S + 1], P.ns[S + 1], T> nxt;
+        pass_tw_load<N, P.rad[S + 1], P.ns[S + 1], P.twoff[S + 1], T>(nxt, tw, active, lane);
+        Sync::sync();
+        if (active) {
+#pragma unroll
+            for (int i = 0; i < RND; ++i) {
+                const int j = lane + i * T;
+                if (NB % T == 0 || i + 1 < RND || j < NB) {
+                    const int k = j % NS, dst = (j - k) * R + k;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) x[cfft_slot<true>(dst + r * NS)] = v[i][r];
+                }
+            }
+        }
+        Sync::sync();
+        cfft_stream_passes<N, INV, S + 1, T, Sync, OUT_LDS>(x, tw, active, lane, nxt, out);
+    } else {
+        if (OUT_LDS) Sync::sync();
+        if (active) {
+#pragma unroll
+            for (int i = 0; i < RND; ++i) {
+                const int j = lane + i * T;
+                if (NB % T == 0 || i + 1 < RND || j < NB) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) out(j + r * NS, v[i][r]);  // NS = NB in the last pass
+                }
+            }
+        }
+        if (OUT_LDS) Sync::sync();
+    }
+}
+
+template <int N, bool INV, int T, class Sync, bool OUT_LDS, class Load, class Out>
+__device__ __forceinline__ void cfft_stream(float2* __restrict__ x, const float2* __restrict__ tw, bool active, int lane,
+                                            Load load, Out out)
+{
+    constexpr CPlan P = CPlanOf<N>::p;
+    static_assert(P.np >= 2, "a first and a last pass");
+    using F = cfft_first<N, T>;
+    PassTw<N, P.rad[1], P.ns[1], T> tw1;
+    pass_tw_load<N, P.rad[1], P.ns[1], P.twoff[1], T>(tw1, tw, active, lane);
+    if (active) {
+        float2 v[F::RND][F::R];
+        load(v);
+#pragma unroll
+        for (int i = 0; i < F::RND; ++i) {
+            butterfly<F::R, INV>(v[i]);
+            if (F::own(lane, i)) {
+                const int j = lane + i * T;
+#pragma unroll
+                for (int r = 0; r < F::R; ++r) x[cfft_slot<true>(j * F::R + r)] = v[i][r];
+            }
+        }
+    }
+    Sync::sync();
+    cfft_stream_passes<N, INV, 1, T, Sync, OUT_LDS>(x, tw, active, lane, tw1, out);
 }
 
 // In-place transform of x[0..N) in LDS (forward: e^{-2 pi i jk/N}, inverse:

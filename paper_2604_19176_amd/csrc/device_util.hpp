@@ -38,6 +38,18 @@ __device__ __forceinline__ void es_weights8(float frac, float (&w)[8])
 
 __device__ __forceinline__ int fbits(float v) { return __float_as_int(v); }
 
+// Sum of v[0..n) in an order fixed by n alone (64 strided partial sums, then a
+// fixed shuffle tree): the same bits for every workgroup size.  Must be
+// reached by all threads of the first wave; the total is returned to lane 0.
+__device__ __forceinline__ float wave0_fixed_sum(const float* __restrict__ v, int n)
+{
+    float s = 0.f;
+    for (int t = threadIdx.x; t < n; t += 64) s += v[t];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+    return s;
+}
+
 // st(t, ld(t)) for t < count by the workgroup (t = t0 + threadIdx.x + j blockDim.x,
 // U values of t per thread and chunk).  A chunk issues all of a thread's loads
 // before its first store, and no load sits under a divergent branch (indices

@@ -48,176 +48,6 @@ __device__ float block_sum(float v, float* scratch)
 // either (col_np, dct_dp <= 16).
 constexpr int kSumClasses = 32;
 
-// Sum of v[0..n) in an order fixed by n alone (64 strided partial sums, then a
-// fixed shuffle tree): the same bits for every workgroup size.  Must be
-// reached by all threads of the first wave; the total is returned to lane 0.
-__device__ __forceinline__ float wave0_fixed_sum(const float* __restrict__ v, int n)
-{
-    float s = 0.f;
-    for (int t = threadIdx.x; t < n; t += 64) s += v[t];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-    return s;
-}
-
-// ---------------------------------------------------------------------------
-// The grid transforms (length Ng, `nseq` sequences at stride ld in LDS): with
-// a compile-time length (plans with grid_spec) sequence s is transformed by
-// threads s T .. s T + T - 1 (T = cfft_lanes(Ng), or twice that for `wide`
-// tiles of one sequence: the same butterflies in the same order on more
-// lanes); else by the run-time plan.
-// ---------------------------------------------------------------------------
-template <int NG, bool INV, int T>
-__device__ __forceinline__ void grid_cfft(const PlanDev& d, float2* x, int ld, int nseq)
-{
-    const int sq = threadIdx.x / T;
-    cfft<NG, INV, T>(x + (size_t)min(sq, nseq - 1) * ld, d.ctw + d.grid_ctw, threadIdx.x - sq * T, sq < nseq);
-}
-
-template <bool INV>
-__device__ __forceinline__ void grid_fft(const PlanDev& d, float2* x, int ld, int nseq, const float2* tb, bool wide)
-{
-    if (d.grid_spec) {
-        switch (d.Ng) {
-#define PAT_GRID_CASE(NG)                                                                        \
-    case NG:                                                                                     \
-        if (wide) grid_cfft<NG, INV, 2 * cfft_lanes(NG)>(d, x, ld, nseq);                       \
-        else grid_cfft<NG, INV, cfft_lanes(NG)>(d, x, ld, nseq);                                 \
-        break;
-            PAT_GRID_LENGTHS(PAT_GRID_CASE)
-#undef PAT_GRID_CASE
-            default: break;
-        }
-    } else {
-        fft_lds<INV>(x, ld, nseq, d.ffts[d.fft_grid], tb);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// forward: column pass (FFT along y of real columns, packed in pairs)
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void colpass_fwd_tile(const PlanDev& d, const WsLayout& L, const float* __restrict__ fb,
-                                                 char* wb, int tile, int NP, float2* sm, float* red_s)
-{
-    const int N = d.N, Ng = d.Ng, CT = 2 * NP;
-    float2* X1 = (float2*)(wb + L.x1);
-    float* red = (float*)(wb + L.red);
-    const int j0 = tile * CT;
-    const float2* tb = fft_twiddles_to_lds(sm + NP * Ng, d.ffts[d.fft_grid], d.tw);
-    for (int e = threadIdx.x; e < NP * Ng; e += blockDim.x) sm[e] = make_float2(0.f, 0.f);
-    __syncthreads();
-    // the tile's columns, masked and deapodised, at rows centred in the padded
-    // column (batched, branch-free loads; columns past N read as zero).
-    // Endpoint term: h^2 times the masked sum of each column, rows in
-    // kSumClasses classes (row i in class i mod kSumClasses), each summed in
-    // order, then the classes in order (independent of the workgroup size and
-    // of the tiling).  With kSumClasses x CT threads each thread's elements are
-    // one column's rows of one class, in order: the class sums are taken from
-    // the values loaded here; else a second loop reads the columns again.
-    const float rcpCT = 1.0f / (float)CT;
-    const bool own_class = (int)blockDim.x == kSumClasses * CT;
-    float csum = 0.f;
-    struct Elt {
-        int i;
-        float v, raw;
-        bool in;
-    };
-    fill_batched<4>(
-        N * CT,
-        [&](int e) {
-            int i, jj;
-            fdivmod(e, CT, rcpCT, i, jj);
-            const int j = j0 + jj, jc = min(j, N - 1);
-            const int2 mr = d.mask_rows[i];
-            const float fv = fb[(size_t)i * N + jc], di = d.deap[i], dj = d.deap[jc];
-            const bool in = j < N && j >= mr.x && j < mr.y;
-            const float v = in ? fv * di * dj : 0.f;
-            int pos = i - N / 2;
-            if (pos < 0) pos += Ng;
-            return Elt{2 * ((jj >> 1) * Ng + pos) + (jj & 1), v, fv, in};
-        },
-        [&](int, Elt el) {
-            ((float*)sm)[el.i] = el.v;
-            csum = el.in ? csum + el.raw : csum;
-        });
-    if (own_class) red_s[threadIdx.x] = csum;  // class threadIdx.x / CT, column threadIdx.x % CT
-    for (int t = threadIdx.x; !own_class && t < kSumClasses * CT; t += blockDim.x) {
-        const int jj = t % CT, c = t / CT, j = j0 + jj, jc = min(j, N - 1);
-        float sc = 0.f;
-        for (int i0 = c; i0 < N; i0 += 4 * kSumClasses) {
-            float v[4];
-            bool in[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int i = i0 + u * kSumClasses, ic = min(i, N - 1);
-                const int2 mr = d.mask_rows[ic];
-                v[u] = fb[(size_t)ic * N + jc];
-                in[u] = i < N && j < N && j >= mr.x && j < mr.y;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) sc = in[u] ? sc + v[u] : sc;
-        }
-        red_s[t] = sc;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < CT && j0 + (int)threadIdx.x < N) {
-        float sc = 0.f;
-        for (int c = 0; c < kSumClasses; ++c) sc += red_s[c * CT + threadIdx.x];
-        red[j0 + threadIdx.x] = sc * d.h2;
-    }
-    __syncthreads();
-    grid_fft<false>(d, sm, Ng, NP, tb, NP == 1);
-    fill_batched<4>(
-        d.Hy * CT,
-        [&](int e) {
-            int r, jj;
-            fdivmod(e, CT, rcpCT, r, jj);
-            const int j = j0 + jj;
-            const int m = r - 4;
-            const int ip = m < 0 ? m + Ng : m;
-            const int in = m > 0 ? Ng - m : -m;
-            const float2 zp = sm[(jj >> 1) * Ng + ip], zn = sm[(jj >> 1) * Ng + in];
-            // even column: (Z(m) + conj Z(-m)) / 2; odd: (Z(m) - conj Z(-m)) / (2i)
-            const float2 o = (jj & 1) == 0 ? make_float2(0.5f * (zp.x + zn.x), 0.5f * (zp.y - zn.y))
-                                           : make_float2(0.5f * (zp.y + zn.y), -0.5f * (zp.x - zn.x));
-            return IdxVal{j < N ? r * N + j : -1, o};
-        },
-        [&](int, IdxVal iv) {
-            if (iv.i >= 0) X1[iv.i] = iv.v;
-        });
-}
-
-// ---------------------------------------------------------------------------
-// forward: row pass (FFT along x)
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void rowpass_fwd_tile(const PlanDev& d, const WsLayout& L, char* wb, int tile, int RPB,
-                                                 float2* sm)
-{
-    const int N = d.N, Ng = d.Ng;
-    const float2* X1 = (const float2*)(wb + L.x1);
-    float2* G = (float2*)(wb + L.grid);
-    const int r0 = tile * RPB;
-    const int nr = min(RPB, d.Hy - r0);
-    const float2* tb = fft_twiddles_to_lds(sm + RPB * Ng, d.ffts[d.fft_grid], d.tw);
-    for (int e = threadIdx.x; e < nr * Ng; e += blockDim.x) sm[e] = make_float2(0.f, 0.f);
-    __syncthreads();
-    const float rcpN = 1.0f / (float)N;
-    fill_batched<4>(
-        nr * N,
-        [&](int e) {
-            int rr, j;
-            fdivmod(e, N, rcpN, rr, j);
-            int pos = j - N / 2;
-            if (pos < 0) pos += Ng;
-            return IdxVal{rr * Ng + pos, X1[(size_t)(r0 + rr) * N + j]};
-        },
-        [&](int, IdxVal iv) { sm[iv.i] = iv.v; });
-    __syncthreads();
-    grid_fft<false>(d, sm, Ng, nr, tb, RPB == 1);
-    fill_batched<4>(
-        nr * Ng, [&](int e) { return sm[e]; }, [&](int e, float2 v) { G[(size_t)r0 * Ng + e] = v; });
-}
-
 // ---------------------------------------------------------------------------
 // forward: ES interpolation of the half spectrum at the half-plane polar
 // points.  Points are visited in band order (sorted by footprint base row r0,
@@ -1327,230 +1157,6 @@ __device__ __forceinline__ void spread_small_tile(const PlanDev& d, const WsLayo
     }
 }
 
-// ---------------------------------------------------------------------------
-// adjoint: row pass (inverse FFT along x, crop to the N image columns)
-// ---------------------------------------------------------------------------
-// Grid row r = 8 q + k takes row tile q's part (its grid row, or, if the tile
-// was split into S runs, the slab rows of the runs that reach relative row k)
-// and, for q >= 1, k < 7 and 8 q < NB (a spread row tile q exists), row tile
-// q - 1's part at relative row k + 8 (its tail row, or its runs' slab rows).
-// Run j of a tile split S ways (w = 8 / S bands) holds relative rows
-// j w .. j w + w + 6 at slab rows s0 + 7 j + (relative row).  The terms are
-// added in one fixed order: (the tile's part, its runs in order) + (the
-// previous tile's part, its runs in order).
-
-// First and last run of a tile split 2^lg ways (lg >= 1) that reach relative
-// row x (0 .. 14): run j covers x when j w <= x <= j w + w + 6, w = 8 / 2^lg.
-__device__ __forceinline__ int2 split_runs_at(int lg, int x)
-{
-    const int w = kSpreadTh >> lg, a = x - w - 6;
-    return make_int2(a > 0 ? (a + w - 1) >> (3 - lg) : 0, min((1 << lg) - 1, x >> (3 - lg)));
-}
-
-__device__ __forceinline__ void rowpass_adj_tile(const PlanDev& d, const WsLayout& L, char* wb, int tile, int RPB,
-                                                 float2* sm)
-{
-    const int N = d.N, Ng = d.Ng;
-    const float2* Gt = (const float2*)(wb + L.grid);
-    float2* X1 = (float2*)(wb + L.x1);
-    const int r0 = tile * RPB;
-    const int nr = min(RPB, d.Hy - r0);
-    const float2* tb = fft_twiddles_to_lds(sm + RPB * Ng, d.ffts[d.fft_grid], d.tw);
-    static_assert(kSpreadTh == 8, "the tail lookup below divides by shifting");
-    const float2* Tl = (const float2*)(wb + L.tail);
-    const float2* Sl = (const float2*)(wb + L.slab);
-    // a row tile's split entry (log2 of its runs, first slab row): q is
-    // uniform over the workgroup, so the entry is a scalar load
-    auto split_of = [&](int q) {
-        const unsigned e = d.spr_head[q];
-        return make_int2((int)(e & 15u), (int)(e >> 4));
-    };
-    // row by row (the row's case is uniform): a whole tile's row plus, if any,
-    // the tail row, four elements' loads per thread in flight; rows of split
-    // tiles sum up to kSpreadMaxRuns slab rows per part
-    constexpr int X = kSpreadMaxRuns;
-    for (int rr = 0; rr < nr; ++rr) {
-        const int r = r0 + rr, q = r >> 3, k = r & 7;
-        const bool tail = q >= 1 && k < 7 && 8 * q < d.NB;
-        const int2 so = split_of(q), st = tail ? split_of(q - 1) : make_int2(0, 0);
-        float2* dst = sm + (size_t)rr * Ng;
-        if (so.x == 0 && st.x == 0) {
-            const float2* __restrict__ gr = Gt + (size_t)r * Ng;
-            if (tail) {
-                const float2* __restrict__ tr = Tl + ((size_t)(q - 1) * 7 + k) * Ng;
-                fill_batched<4>(
-                    Ng,
-                    [&](int c) {
-                        const float2 a = gr[c], t = tr[c];
-                        return make_float2(a.x + t.x, a.y + t.y);
-                    },
-                    [&](int c, float2 v) { dst[c] = v; });
-            } else {
-                fill_batched<4>(Ng, [&](int c) { return gr[c]; }, [&](int c, float2 v) { dst[c] = v; });
-            }
-            continue;
-        }
-        // the parts' rows: no own rows (the grid row, or the runs 0 .. nho of a
-        // split tile) and nt tail rows (the tail row, or the previous tile's runs
-        // jt.x .. jt.y); unused slots repeat the first row and are not added
-        const float2* po[X];
-        const float2* pt[X];
-        int no, nt;
-        if (so.x) {
-            no = split_runs_at(so.x, k).y + 1;
-#pragma unroll
-            for (int j = 0; j < X; ++j) po[j] = Sl + (size_t)(so.y + 7 * (j < no ? j : 0) + k) * Ng;
-        } else {
-            no = 1;
-#pragma unroll
-            for (int j = 0; j < X; ++j) po[j] = Gt + (size_t)r * Ng;
-        }
-        if (st.x) {
-            const int2 jt = split_runs_at(st.x, k + 8);
-            nt = jt.y - jt.x + 1;
-#pragma unroll
-            for (int j = 0; j < X; ++j) pt[j] = Sl + (size_t)(st.y + 7 * (jt.x + (j < nt ? j : 0)) + k + 8) * Ng;
-        } else {
-            nt = tail ? 1 : 0;
-#pragma unroll
-            for (int j = 0; j < X; ++j) pt[j] = tail ? Tl + ((size_t)(q - 1) * 7 + k) * Ng : po[0];
-        }
-        fill_batched<2>(
-            Ng,
-            [&](int c) {
-                float2 a[X], b[X];
-#pragma unroll
-                for (int j = 0; j < X; ++j) {
-                    a[j] = po[j][c];
-                    b[j] = pt[j][c];
-                }
-                float2 o = a[0], t = b[0];
-#pragma unroll
-                for (int j = 1; j < X; ++j) {
-                    if (j < no) o = make_float2(o.x + a[j].x, o.y + a[j].y);
-                    if (j < nt) t = make_float2(t.x + b[j].x, t.y + b[j].y);
-                }
-                return nt ? make_float2(o.x + t.x, o.y + t.y) : o;
-            },
-            [&](int c, float2 v) { dst[c] = v; });
-    }
-    __syncthreads();
-    grid_fft<true>(d, sm, Ng, nr, tb, RPB == 1);
-    const float rcpN = 1.0f / (float)N;
-    fill_batched<4>(
-        nr * N,
-        [&](int e) {
-            int rr, j;
-            fdivmod(e, N, rcpN, rr, j);
-            int pos = j - N / 2;
-            if (pos < 0) pos += Ng;
-            return sm[rr * Ng + pos];
-        },
-        [&](int e, float2 v) { X1[(size_t)r0 * N + e] = v; });
-}
-
-// ---------------------------------------------------------------------------
-// adjoint: column pass (Hermitian symmetrisation, inverse FFT along y, real
-// parts of two columns packed as one complex transform, crop, deapodise, mask)
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ void colpass_adj_tile(const PlanDev& d, const WsLayout& L, char* wb, float* __restrict__ fb,
-                                                 int tile, int NP, int n_sum, float2* sm, float* gsum_s)
-{
-    const int N = d.N, Ng = d.Ng, CT = 2 * NP;
-    const float2* X1 = (const float2*)(wb + L.x1);
-    const float* red = (const float*)(wb + L.red);
-    if (threadIdx.x < 64) {
-        const float s = wave0_fixed_sum(red, n_sum);
-        if (threadIdx.x == 0) *gsum_s = s;
-    }
-    const int j0 = tile * CT;
-    const int top = Ng / 2 + 4;
-    const float2* tb = fft_twiddles_to_lds(sm + NP * Ng, d.ffts[d.fft_grid], d.tw);
-    // column pair p at residue q: batched loads with rows and columns clamped
-    // into the stored range, values outside it selected as zero
-    const float rcpNg = 1.0f / (float)Ng;
-    fill_batched<4>(
-        NP * Ng,
-        [&](int e) {
-            int p, q;
-            fdivmod(e, Ng, rcpNg, p, q);
-            const int ja = j0 + 2 * p, jb = ja + 1;
-            // stored row of residue q and of -q (or -1 if not stored)
-            const int rq = q <= top ? q + 4 : (q >= Ng - 4 ? q - Ng + 4 : -1);
-            const int qn = q == 0 ? 0 : Ng - q;
-            const int rn = qn <= top ? qn + 4 : (qn >= Ng - 4 ? qn - Ng + 4 : -1);
-            const int rqc = max(rq, 0), rnc = max(rn, 0), jac = min(ja, N - 1), jbc = min(jb, N - 1);
-            const float2 z0 = make_float2(0.f, 0.f);
-            const float2 la = X1[(size_t)rqc * N + jac], lna = X1[(size_t)rnc * N + jac];
-            const float2 lb = X1[(size_t)rqc * N + jbc], lnb = X1[(size_t)rnc * N + jbc];
-            const float2 ua = (ja < N && rq >= 0) ? la : z0, una = (ja < N && rn >= 0) ? lna : z0;
-            const float2 ub = (jb < N && rq >= 0) ? lb : z0, unb = (jb < N && rn >= 0) ? lnb : z0;
-            // z = (ua + conj una)/2 + i (ub + conj unb)/2
-            const float2 ha = make_float2(0.5f * (ua.x + una.x), 0.5f * (ua.y - una.y));
-            const float2 hb = make_float2(0.5f * (ub.x + unb.x), 0.5f * (ub.y - unb.y));
-            return make_float2(ha.x - hb.y, ha.y + hb.x);
-        },
-        [&](int e, float2 v) { sm[e] = v; });
-    __syncthreads();
-    grid_fft<true>(d, sm, Ng, NP, tb, NP == 1);
-    const float kt = d.kappa * d.h2 * *gsum_s;
-    const float rcpCT = 1.0f / (float)CT;
-    fill_batched<4>(
-        N * CT,
-        [&](int e) {
-            int i, jj;
-            fdivmod(e, CT, rcpCT, i, jj);
-            const int j = j0 + jj, jc = min(j, N - 1);
-            int pos = i - N / 2;
-            if (pos < 0) pos += Ng;
-            const float2 z = sm[(jj >> 1) * Ng + pos];
-            const float c = (jj & 1) ? z.y : z.x;
-            const int2 mr = d.mask_rows[i];
-            const float di = d.deap[i], dj = d.deap[jc];
-            const float v = (j >= mr.x && j < mr.y) ? di * dj * c + kt : 0.f;
-            return IdxF{j < N ? i * N + j : -1, v};
-        },
-        [&](int, IdxF iv) {
-            if (iv.i >= 0) fb[iv.i] = iv.v;
-        });
-}
-
-__global__ __launch_bounds__(1024) void k_colpass_fwd(PlanDev d, WsLayout L, const float* __restrict__ f,
-                                                     InstPtrs wsp, int NP)
-{
-    extern __shared__ float2 sm[];
-    __shared__ float red_s[1024];
-    const int b = blockIdx.y;
-    colpass_fwd_tile(d, L, f + (size_t)b * d.N * d.N, wsp.ws + (size_t)b * wsp.stride, blockIdx.x, NP, sm, red_s);
-}
-
-__global__ __launch_bounds__(1024) void k_colpass_fwd_b(BatchDev bt, const float* const* __restrict__ fin, char* ws)
-{
-    extern __shared__ float2 sm[];
-    __shared__ float red_s[1024];
-    int i, tile;
-    if (!batch_item(bt, kStCol, i, tile)) return;
-    const BatchInst& I = bt.inst[i];
-    const PlanDev d = I.d;
-    colpass_fwd_tile(d, I.L, fin[i], ws + I.ws_off, tile, I.col_np, sm, red_s);
-}
-
-__global__ __launch_bounds__(1024) void k_rowpass_fwd(PlanDev d, WsLayout L, InstPtrs wsp, int RPB)
-{
-    extern __shared__ float2 sm[];
-    rowpass_fwd_tile(d, L, wsp.ws + (size_t)blockIdx.y * wsp.stride, blockIdx.x, RPB, sm);
-}
-
-__global__ __launch_bounds__(1024) void k_rowpass_fwd_b(BatchDev bt, char* ws)
-{
-    extern __shared__ float2 sm[];
-    int i, tile;
-    if (!batch_item(bt, kStRow, i, tile)) return;
-    const BatchInst& I = bt.inst[i];
-    const PlanDev d = I.d;
-    rowpass_fwd_tile(d, I.L, ws + I.ws_off, tile, I.row_rpb, sm);
-}
-
 template <int IB, int CB>
 __global__ __launch_bounds__(kGatherThreads) void k_gather(PlanDev d, WsLayout L, InstPtrs wsp, int TH, int batch)
 {
@@ -1722,43 +1328,6 @@ __global__ __launch_bounds__(CB) void k_spread_b(BatchDev bt, char* ws)
     const PlanDev d = I.d;
     char* const wbs[1] = {ws + I.ws_off};
     spread_tile<1, CB>(d, I.L, wbs, 1, tile, sf);
-}
-
-__global__ __launch_bounds__(1024) void k_rowpass_adj(PlanDev d, WsLayout L, InstPtrs wsp, int RPB)
-{
-    extern __shared__ float2 sm[];
-    rowpass_adj_tile(d, L, wsp.ws + (size_t)blockIdx.y * wsp.stride, blockIdx.x, RPB, sm);
-}
-
-__global__ __launch_bounds__(1024) void k_rowpass_adj_b(BatchDev bt, char* ws)
-{
-    extern __shared__ float2 sm[];
-    int i, tile;
-    if (!batch_item(bt, kStRow, i, tile)) return;
-    const BatchInst& I = bt.inst[i];
-    const PlanDev d = I.d;
-    rowpass_adj_tile(d, I.L, ws + I.ws_off, tile, I.row_rpb, sm);
-}
-
-__global__ __launch_bounds__(1024) void k_colpass_adj(PlanDev d, WsLayout L, InstPtrs wsp, float* __restrict__ f,
-                                                     int NP, int n_sum)
-{
-    extern __shared__ float2 sm[];
-    __shared__ float gsum_s;
-    const int b = blockIdx.y;
-    colpass_adj_tile(d, L, wsp.ws + (size_t)b * wsp.stride, f + (size_t)b * d.N * d.N, blockIdx.x, NP, n_sum, sm,
-                     &gsum_s);
-}
-
-__global__ __launch_bounds__(1024) void k_colpass_adj_b(BatchDev bt, char* ws, float* const* __restrict__ fout)
-{
-    extern __shared__ float2 sm[];
-    __shared__ float gsum_s;
-    int i, tile;
-    if (!batch_item(bt, kStCol, i, tile)) return;
-    const BatchInst& I = bt.inst[i];
-    const PlanDev d = I.d;
-    colpass_adj_tile(d, I.L, ws + I.ws_off, fout[i], tile, I.col_np, d.D, sm, &gsum_s);
 }
 
 // ---------------------------------------------------------------------------

@@ -304,8 +304,10 @@ struct BatchInst {
     PlanDev d;
     WsLayout L;
     size_t ws_off;    // byte offset of the instance's workspace in the batch workspace
-    int col_np, row_rpb, ring_rt, dct_dp, gat_th;
+    int col_np, row_rpb, ring_rt, dct_dp, gat_th;  // (col_np, row_rpb: np_col, np_row of the plan)
     int n_col_tiles, n_pair_tiles;
+    unsigned thr_col, thr_row;  // workgroup sizes and LDS of the instance's 2D-FFT passes
+    size_t lds_col, lds_row;
 };
 
 struct BatchDev {
@@ -334,7 +336,9 @@ struct pat_plan {
     void* table_mem;        // one device allocation holding every table
     int n_col_tiles;        // column-pass tiles (mass partials)
     int n_pair_tiles;       // cosine-transform tiles (data-sum partials)
+    int np_col, np_row;     // column pairs / rows per 2D-FFT workgroup (cfg.col_np, cfg.row_rpb as far as they fit)
     int thr_col, thr_row, thr_ring, thr_dct;  // workgroup sizes of the FFT kernels
+    size_t lds_col, lds_row;  // dynamic LDS of the 2D-FFT passes
     size_t lds_ring;        // dynamic LDS of the ring kernels
     double* det_theta;      // copy of the explicit detector angles (NULL for a uniform arc)
     // optional per-kernel timing (pat_profile_enable): events around each launch
@@ -365,11 +369,21 @@ inline unsigned xcd_grid(int items) { return (unsigned)(((items + kXcds - 1) / k
 // Launches of the ring kernels (ring_fwd.hip, ring_adj.hip).
 void ring_fwd_launch(const pat_plan* p, const InstPtrs& wsp, int batch, hipStream_t st);
 void ring_adj_launch(const pat_plan* p, const InstPtrs& wsp, int batch, hipStream_t st);
+// Launches of the 2D-FFT passes (grid_fwd.hip, grid_adj.hip); hi: some instance's
+// compile-time grid side is above 1024.
+void colpass_fwd_launch(const pat_plan* p, const float* f, const InstPtrs& wsp, int batch, hipStream_t st);
+void rowpass_fwd_launch(const pat_plan* p, const InstPtrs& wsp, int batch, hipStream_t st);
+void rowpass_adj_launch(const pat_plan* p, const InstPtrs& wsp, int batch, hipStream_t st);
+void colpass_adj_launch(const pat_plan* p, const InstPtrs& wsp, float* f, int batch, hipStream_t st);
+void colpass_fwd_b_launch(const BatchDev& bt, const float* const* f, char* ws, int items, unsigned thr, size_t lds, bool hi,
+                          hipStream_t st);
+void rowpass_fwd_b_launch(const BatchDev& bt, char* ws, int items, unsigned thr, size_t lds, bool hi, hipStream_t st);
+void rowpass_adj_b_launch(const BatchDev& bt, char* ws, int items, unsigned thr, size_t lds, bool hi, hipStream_t st);
+void colpass_adj_b_launch(const BatchDev& bt, char* ws, float* const* f, int items, unsigned thr, size_t lds, bool hi,
+                          hipStream_t st);
 void ring_fwd_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, hipStream_t st);
 void ring_adj_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, hipStream_t st);
 
-// Threads of a 2D-FFT pass workgroup over `nseq` sequences of the plan's grid side.
-int grid_threads(const pat_plan* p, int nseq);
 }  // namespace pat
 
 // A heterogeneous batch (pat_batch_create).
@@ -386,4 +400,5 @@ struct pat_batch {
     // per-stage workgroup size and dynamic LDS (maxima over the instances)
     unsigned thr_col = 0, thr_row = 0, thr_ring = 0, thr_dct = 0;
     size_t lds_col = 0, lds_row = 0, lds_ring = 0, lds_dct = 0;
+    bool grid_hi = false;              // a compile-time grid side above 1024 among the instances
 };

@@ -484,15 +484,6 @@ int fixed_fft_for(long n, FftDev* out, std::vector<float2>& tw)
 
 int fft_workgroup_threads(int nseq, const FftDev& fd) { return fft_threads(nseq, fd); }
 
-// Threads of a 2D-FFT pass workgroup over `nseq` sequences of the plan's grid side
-// (compile-time lengths: a tile of one sequence gets twice the transform's
-// lanes, which shortens the single-instance chain; the kernels pass `wide`
-// to the transform when their tile has one sequence)
-int grid_threads(const pat_plan* p, int nseq)
-{
-    return p->dev.grid_spec ? (nseq == 1 ? 2 : nseq) * cfft_lanes(p->dev.Ng) : fft_threads(nseq, p->h_fft_grid);
-}
-
 // Dynamic LDS of the ring kernels: half-ring FFT buffer, synthesis buffers,
 // [D][RT] detector tile and four twiddle tables.
 static size_t ring_lds_bytes(const PlanDev& d, int RT)
@@ -515,7 +506,8 @@ int apply_launch(pat_plan* p, const LaunchCfg& c)
         return v >= 1 && v <= 16 && v * each + fixed <= kLdsMax && fft_threads(v, f) <= 1024;
     };
     auto grid_ok = [&](int v) {
-        if (!d.grid_spec) return fft_ok(v, sizeof(float2) * d.Ng, p->h_fft_grid, twb_bytes(p->h_fft_grid));
+        const bool pow2 = (d.Ng & (d.Ng - 1)) == 0;
+        if (!d.grid_spec || !pow2) return fft_ok(v, sizeof(float2) * d.Ng, p->h_fft_grid, twb_bytes(p->h_fft_grid));
         return v >= 1 && v <= 16 && v * sizeof(float2) * d.Ng + twb_bytes(p->h_fft_grid) <= kLdsMax &&
                (v == 1 ? 2 : v) * cfft_lanes(d.Ng) <= 1024;
     };
@@ -535,10 +527,31 @@ int apply_launch(pat_plan* p, const LaunchCfg& c)
     // compile-time ring kernels: ring_rt >= 2 gives the rings of the short-length
     // group two waves each (the same arithmetic on more lanes)
     if (d.ring_spec) p->thr_ring = ring_spec_threads(d.ring_spec_grp, d.ring_spec_grp == 0 && c.ring_rt >= 2 ? 2 : 1);
-    p->thr_col = grid_threads(p, c.col_np);
-    p->thr_row = grid_threads(p, c.row_rpb);
+    // 2D-FFT passes: as many sequences per workgroup as asked for and as fit
+    if (d.grid_spec) {
+        const int T = cfft_lanes(d.Ng);
+        auto col_lds = [&](int v) {
+            return sizeof(float2) * (size_t)v * grid_col_ld(d.Ng) + sizeof(float) * 2 * (size_t)v * (T + kColSumGroups);
+        };
+        auto row_lds = [&](int v) { return sizeof(float2) * (size_t)v * cfft_padded_len(d.Ng); };
+        p->np_col = c.col_np;
+        while (p->np_col > 1 && (p->np_col * T > 1024 || col_lds(p->np_col) > kLdsMax)) --p->np_col;
+        p->np_row = c.row_rpb;
+        while (p->np_row > 1 && (p->np_row * T > 1024 || row_lds(p->np_row) > kLdsMax)) --p->np_row;
+        p->thr_col = p->np_col * T;
+        p->thr_row = p->np_row * T;
+        p->lds_col = col_lds(p->np_col);
+        p->lds_row = row_lds(p->np_row);
+    } else {
+        p->np_col = c.col_np;
+        p->np_row = c.row_rpb;
+        p->thr_col = fft_threads(c.col_np, p->h_fft_grid);
+        p->thr_row = fft_threads(c.row_rpb, p->h_fft_grid);
+        p->lds_col = sizeof(float2) * (size_t)c.col_np * d.Ng + twb_bytes(p->h_fft_grid);
+        p->lds_row = sizeof(float2) * (size_t)c.row_rpb * d.Ng + twb_bytes(p->h_fft_grid);
+    }
     p->thr_dct = d.dct_spec ? c.dct_dp * cfft_lanes(2 * d.M) : fft_threads(c.dct_dp, p->h_fft_dct);
-    p->n_col_tiles = (d.N + 2 * c.col_np - 1) / (2 * c.col_np);
+    p->n_col_tiles = (d.N + 2 * p->np_col - 1) / (2 * p->np_col);
     p->n_pair_tiles = ((d.D + 1) / 2 + c.dct_dp - 1) / c.dct_dp;
     return PAT_OK;
 }

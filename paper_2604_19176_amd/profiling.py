@@ -172,7 +172,7 @@ def traffic(fetch_csv, write_csv, kernel, calib_bytes, rdreq=None):
 
 
 # the device sources every kernel is compiled from
-KERNEL_FILES = ("kernels.hip", "ring_fwd.hip", "ring_adj.hip", "ring.hpp", "device_util.hpp", "fft.hpp", "cfft.hpp",
+KERNEL_FILES = ("kernels.hip", "grid_fwd.hip", "grid_adj.hip", "grid.hpp", "ring_fwd.hip", "ring_adj.hip", "ring.hpp", "device_util.hpp", "fft.hpp", "cfft.hpp",
                 "pat_internal.hpp")
 
 
