@@ -537,10 +537,12 @@ static void batch_layout(pat_batch* b)
     b->base.assign((size_t)kNumStages * (n + 1), 0);
     b->thr_col = b->thr_row = b->thr_ring = b->thr_dct = 0;
     b->lds_col = b->lds_row = b->lds_ring = b->lds_dct = 0;
+    b->ring_grp = 0;
     for (int i = 0; i < n; ++i) {
         BatchInst& I = b->inst[i];
         const pat_plan* p = b->plans[i];
         const PlanDev& d = I.d;
+        b->ring_grp = b->ring_grp < 0 || !d.ring_spec ? -1 : std::max(b->ring_grp, d.ring_spec_grp);
         I.gat_th = b->gat_th;
         int items[kNumStages];
         items[kStCol] = I.n_col_tiles;
@@ -707,7 +709,7 @@ extern "C" int pat_batch_forward(const pat_batch* b, const float* const* f_ptrs,
         }
     }
     if ((rc = check_launch())) return rc;
-    ring_fwd_b_launch(bt, w, batch_items(b, kStRing), b->thr_ring, b->lds_ring, st);
+    ring_fwd_b_launch(bt, w, batch_items(b, kStRing), b->thr_ring, b->lds_ring, b->ring_grp, st);
     if ((rc = check_launch())) return rc;
     if (batch_items(b, kStSynFwd) > 0) {
         hipLaunchKernelGGL(k_syn_dense_fwd_b, dim3(xcd_grid(batch_items(b, kStSynFwd))), dim3(kSynThreads), 0, st,
@@ -735,7 +737,7 @@ extern "C" int pat_batch_adjoint(const pat_batch* b, const float* const* g_ptrs,
                            bt, w);
         if ((rc = check_launch())) return rc;
     }
-    ring_adj_b_launch(bt, w, batch_items(b, kStRing), b->thr_ring, b->lds_ring, st);
+    ring_adj_b_launch(bt, w, batch_items(b, kStRing), b->thr_ring, b->lds_ring, b->ring_grp, st);
     if ((rc = check_launch())) return rc;
     if (batch_items(b, kStSpreadSmall) > 0) {
         hipLaunchKernelGGL(k_spread_small_b, dim3(xcd_grid(batch_items(b, kStSpreadSmall))), dim3(kSprWaves * 64),

@@ -114,6 +114,7 @@ __host__ __device__ constexpr CPlan make_cplan(int n)
 // lengths up to kCfftSplit and once for all of them, so that plans whose ring
 // and synthesis lengths are all short get the register budget of short ones.
 constexpr int kCfftSplit = 512;
+constexpr int kCfftMaxLen1 = 1024;  // longest one-wave length
 #define PAT_CFFT_LENGTHS_LO(X)                                                                                \
     X(2) X(3) X(4) X(6) X(8) X(9) X(12) X(16) X(18) X(24) X(27) X(32) X(36) X(48) X(54) X(64) X(72) X(81) \
     X(96) X(108) X(128) X(144) X(162) X(192) X(216) X(243) X(256) X(288) X(324) X(384) X(432) X(486) X(512)
@@ -125,6 +126,9 @@ constexpr int kCfftSplit = 512;
 // Threads of a ring workgroup of length group G (0: lengths up to kCfftSplit,
 // 1: up to 1024, 2: up to 2048), W waves per ring in the one-wave groups
 __host__ __device__ constexpr int ring_spec_threads(int G, int W = 1) { return G == 2 ? 2 * kCfftLanes : W * kCfftLanes; }
+
+// Longest length of a group
+__host__ __device__ constexpr int ring_spec_max(int G) { return G == 2 ? 2 * kCfftMaxLen1 : G == 1 ? kCfftMaxLen1 : kCfftSplit; }
 
 // The column passes' sums of a column: over a sequence's lanes in kColSumGroups
 // groups, then over the groups, one order for every tile shape.

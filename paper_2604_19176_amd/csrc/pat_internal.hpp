@@ -209,11 +209,11 @@ constexpr int kRingMaxThreads = 256;
 // synthesis buffer), synthesis buffer, two-level twiddle tables of lengths
 // Npsi_max and S.
 __host__ __device__ constexpr int ring_tw_slots(int n) { return 64 + (n + 63) / 64; }
-// With compile-time transforms: the ring buffer (Npsi_max/2 values), then the
-// synthesis transform's P/2 and one more slot (the adjoint's value at P/2).
+// With compile-time transforms: one buffer for the ring transform (Npsi_max/2
+// values) and the synthesis transform (P/2 and the adjoint's value at P/2).
 __host__ __device__ constexpr size_t ring_spec_lds_slots(int npsi_max, int S)
 {
-    return (size_t)(npsi_max / 2) + (size_t)(S / 2) + 1;
+    return (size_t)(npsi_max / 2 > S / 2 + 1 ? npsi_max / 2 : S / 2 + 1);
 }
 __host__ __device__ constexpr size_t ring_lds_slots(int npsi_max, int S, int syn_half)
 {
@@ -366,7 +366,8 @@ struct InstPtrs {
 constexpr int kXcds = 8;
 inline unsigned xcd_grid(int items) { return (unsigned)(((items + kXcds - 1) / kXcds) * kXcds); }
 
-// Launches of the ring kernels (ring_fwd.hip, ring_adj.hip).
+// Launches of the ring kernels (ring_fwd.hip, ring_adj.hip); spec_grp: the largest
+// length group if every instance has compile-time transforms, else -1.
 void ring_fwd_launch(const pat_plan* p, const InstPtrs& wsp, int batch, hipStream_t st);
 void ring_adj_launch(const pat_plan* p, const InstPtrs& wsp, int batch, hipStream_t st);
 // Launches of the 2D-FFT passes (grid_fwd.hip, grid_adj.hip); hi: some instance's
@@ -381,8 +382,8 @@ void rowpass_fwd_b_launch(const BatchDev& bt, char* ws, int items, unsigned thr,
 void rowpass_adj_b_launch(const BatchDev& bt, char* ws, int items, unsigned thr, size_t lds, bool hi, hipStream_t st);
 void colpass_adj_b_launch(const BatchDev& bt, char* ws, float* const* f, int items, unsigned thr, size_t lds, bool hi,
                           hipStream_t st);
-void ring_fwd_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, hipStream_t st);
-void ring_adj_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, hipStream_t st);
+void ring_fwd_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, int spec_grp, hipStream_t st);
+void ring_adj_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, int spec_grp, hipStream_t st);
 
 }  // namespace pat
 
@@ -400,5 +401,6 @@ struct pat_batch {
     // per-stage workgroup size and dynamic LDS (maxima over the instances)
     unsigned thr_col = 0, thr_row = 0, thr_ring = 0, thr_dct = 0;
     size_t lds_col = 0, lds_row = 0, lds_ring = 0, lds_dct = 0;
+    int ring_grp = -1;                 // length group of the compile-time ring kernels, -1: some instance has none
     bool grid_hi = false;              // a compile-time grid side above 1024 among the instances
 };

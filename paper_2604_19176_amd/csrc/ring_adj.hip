@@ -178,9 +178,10 @@ __device__ __forceinline__ void ring_adj_spec_head(const PlanDev& d, const float
     __syncthreads();
 }
 
+// The ring transform's input takes the place of the synthesis values in buf
+// (held in registers across the barrier), as in the forward kernel.
 template <int Pn, int T>
-__device__ __forceinline__ void ring_adj_spec_tail(const PlanDev& d, const RingSpecArgs& a, float2* syn,
-                                                   float2* buf, float2* Hb)
+__device__ __forceinline__ void ring_adj_spec_tail(const PlanDev& d, const RingSpecArgs& a, float2* buf, float2* Hb)
 {
     const int lane = threadIdx.x;
     const bool act = lane < T;
@@ -198,7 +199,7 @@ __device__ __forceinline__ void ring_adj_spec_tail(const PlanDev& d, const RingS
     //   y~_s = sm/2 - (i/2) t,  y~_{SH-s} = conj(sm)/2 - (i/2) conj(t),
     // and y~_{SH} = Re Z_0 - Im Z_0; above P/2, y~_{P-q} = conj y~_q
     // (each lane reads and writes only its own pair's slots)
-    float2* ys = syn;
+    float2* ys = buf;
     if (act) {
         const int PAIRS = SH / 2 + 1;  // s = 0 .. SH/2
         for (int s = lane; s < PAIRS; s += T) {
@@ -236,19 +237,27 @@ __device__ __forceinline__ void ring_adj_spec_tail(const PlanDev& d, const RingS
     // item u < (Pn + 1)/2 writes slots u and Pn - u; item 0 writes slot 0 and,
     // for even Pn, slot Pn/2 (one path for every lane: no branch on u, the
     // loads of all rounds can be issued together)
-    constexpr int items = (Pn + 1) / 2;
+    constexpr int items = (Pn + 1) / 2, NI = (items + T - 1) / T;
+    float2 ha[NI], hb[NI];
     if (act) {
 #pragma unroll
-        for (int i = 0; i < (items + T - 1) / T; ++i) {
-            const int u0 = lane + i * T;
-            const bool own = items % T == 0 || u0 < items;
-            const int u = min(u0, items - 1);
+        for (int i = 0; i < NI; ++i) {
+            const int u = min(lane + i * T, items - 1);
             const int u2 = u == 0 ? ((Pn & 1) == 0 ? Pn / 2 : 0) : Pn - u;  // the second slot
             const float2 qa = qmode(u), qb = qmode(u2);
-            const float2 ha = herm(u, qa, qb), hb = herm(u2, qb, u == 0 ? qb : qa);
-            if (own) {
-                buf[u] = ha;
-                if (u2 != 0) buf[u2] = hb;
+            ha[i] = herm(u, qa, qb);
+            hb[i] = herm(u2, qb, u == 0 ? qb : qa);
+        }
+    }
+    __syncthreads();
+    if (act) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int u = lane + i * T;
+            const int u2 = u == 0 ? ((Pn & 1) == 0 ? Pn / 2 : 0) : Pn - u;
+            if (items % T == 0 || u < items) {
+                buf[u] = ha[i];
+                if (u2 != 0) buf[u2] = hb[i];
             }
         }
     }
@@ -278,15 +287,14 @@ __device__ __forceinline__ void ring_adj_spec_tile(const PlanDev& d, const WsLay
 {
     const float* hT = (const float*)(wb + L.hdet);  // [nlam][D]
     float2* Hb = (float2*)(wb + L.polar);
-    float2* syn = buf + d.npsi_max / 2;  // the synthesis transform after the ring buffer
     constexpr int T = ring_spec_threads(G, W);
-    ring_adj_spec_head<T>(d, hT + (size_t)n * d.D, syn);
-    cfft_run_wg<false, G, T>(syn, d.fold_P >> 1, d.ctw + d.syn_ctw);
+    ring_adj_spec_head<T>(d, hT + (size_t)n * d.D, buf);
+    cfft_run_wg<false, G, T>(buf, d.fold_P >> 1, d.ctw + d.syn_ctw);
     const RingSpecArgs a = ring_spec_args(d, n);
     const int Pn = d.ring_off[n + 1] - a.off;
     switch (Pn) {
 #define PAT_RING_ADJ_TAIL(LEN) \
-    case LEN: ring_adj_spec_tail<LEN, T>(d, a, syn, buf, Hb); break;
+    case LEN: ring_adj_spec_tail<LEN, T>(d, a, buf, Hb); break;
         PAT_CFFT_LENGTHS_LO(PAT_RING_ADJ_TAIL)
         default:
             if constexpr (G >= 1) {
@@ -353,10 +361,28 @@ void ring_adj_launch(const pat_plan* p, const InstPtrs& wsp, int batch, hipStrea
     else hipLaunchKernelGGL(k_ring_adj, grid, blk, p->lds_ring, st, d, p->ws, wsp, p->cfg.ring_rt, batch);
 }
 
-// The ring kernel of a heterogeneous batch of `items` work items.
-void ring_adj_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, hipStream_t st)
+// Heterogeneous batches whose instances all have compile-time transforms: one
+// ring per workgroup of the largest instance's length group, without the
+// run-time form's registers and workgroup size.
+template <int G>
+__global__ __launch_bounds__(ring_spec_threads(G)) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_adj_spec_b(BatchDev bt, char* ws)
 {
-    hipLaunchKernelGGL(k_ring_adj_b, dim3(xcd_grid(items)), dim3(threads), lds, st, bt, ws);
+    extern __shared__ float2 sm[];
+    int i, tile;
+    if (!batch_item(bt, kStRing, i, tile)) return;
+    const BatchInst& I = bt.inst[i];
+    const PlanDev d = I.d;
+    ring_adj_spec_tile<G, 1>(d, I.L, ws + I.ws_off, d.nlam - 1 - tile, sm);  // largest rings first
+}
+
+// The ring kernel of a heterogeneous batch of `items` work items.
+void ring_adj_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, int spec_grp, hipStream_t st)
+{
+    const dim3 grid(xcd_grid(items));
+    if (spec_grp == 0) hipLaunchKernelGGL(k_ring_adj_spec_b<0>, grid, dim3(ring_spec_threads(0)), lds, st, bt, ws);
+    else if (spec_grp == 1) hipLaunchKernelGGL(k_ring_adj_spec_b<1>, grid, dim3(ring_spec_threads(1)), lds, st, bt, ws);
+    else if (spec_grp == 2) hipLaunchKernelGGL(k_ring_adj_spec_b<2>, grid, dim3(ring_spec_threads(2)), lds, st, bt, ws);
+    else hipLaunchKernelGGL(k_ring_adj_b, grid, dim3(threads), lds, st, bt, ws);
 }
 
 }  // namespace pat

@@ -131,9 +131,13 @@ __device__ __forceinline__ float2 syn_prologue(float2 y1, float2 y1m, float2 y2,
     return make_float2(E.x - O.y, E.y + O.x);
 }
 
-template <int Pn, int T>
+// SHM: longest half-length synthesis of the length group.  The synthesis input
+// takes the place of the modes in buf (held in registers across the barrier):
+// one buffer of max(Npsi_max / 2, P / 2) values per ring keeps twice as many rings
+// resident.
+template <int Pn, int T, int SHM>
 __device__ __forceinline__ void ring_fwd_spec_head(const PlanDev& d, const float2* __restrict__ Fp,
-                                                   const RingSpecArgs& a, float2* buf, float2* syn)
+                                                   const RingSpecArgs& a, float2* buf)
 {
     const int lane = threadIdx.x;
     const bool act = lane < T;
@@ -195,17 +199,33 @@ __device__ __forceinline__ void ring_fwd_spec_head(const PlanDev& d, const float
     };
     const float2* __restrict__ sw = d.ctw + d.syn_sw;
     const int items = (SH + 1) >> 1;
+    constexpr int NI = (SHM / 2 + T - 1) / T;
+    float2 oa[NI], ob[NI];  // inputs s and SH - s (s = 0: 0 and SH / 2)
     if (act) {
-        for (int s = lane; s < items; s += T) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int s = lane + i * T;
+            if (s >= items) continue;
             if (s == 0) {
                 const float2 y0 = mode(0), yh = mode(SH), yq = mode(SH >> 1), y3 = mode(SH + (SH >> 1));
-                syn[0] = syn_prologue(y0, y0, yh, yh, sw[0]);
-                if ((SH & 1) == 0) syn[SH >> 1] = syn_prologue(yq, y3, y3, yq, sw[SH >> 1]);
+                oa[i] = syn_prologue(y0, y0, yh, yh, sw[0]);
+                ob[i] = syn_prologue(yq, y3, y3, yq, sw[SH >> 1]);
             } else {
                 const float2 ya = mode(s), yb = mode(Pf - s), yc = mode(s + SH), yd = mode(SH - s);
-                syn[s] = syn_prologue(ya, yb, yc, yd, sw[s]);
-                syn[SH - s] = syn_prologue(yd, yc, yb, ya, sw[SH - s]);
+                oa[i] = syn_prologue(ya, yb, yc, yd, sw[s]);
+                ob[i] = syn_prologue(yd, yc, yb, ya, sw[SH - s]);
             }
+        }
+    }
+    __syncthreads();
+    if (act) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int s = lane + i * T;
+            if (s >= items) continue;
+            buf[s] = oa[i];
+            if (s != 0) buf[SH - s] = ob[i];
+            else if ((SH & 1) == 0) buf[SH >> 1] = ob[i];
         }
     }
     __syncthreads();
@@ -243,13 +263,12 @@ __device__ __forceinline__ void ring_fwd_spec_tile(const PlanDev& d, const WsLay
     // synthesis twiddles live across it
     const float2* __restrict__ Fp = (const float2*)(wb + L.polar);
     float* hT = (float*)(wb + L.hdet);  // [nlam][D]
-    float2* syn = buf + d.npsi_max / 2;  // the synthesis input after the ring buffer
     const RingSpecArgs a = ring_spec_args(d, n);
     const int Pn = d.ring_off[n + 1] - a.off;
-    constexpr int T = ring_spec_threads(G, W);
+    constexpr int T = ring_spec_threads(G, W), SHM = ring_spec_max(G);
     switch (Pn) {
 #define PAT_RING_FWD_HEAD(LEN) \
-    case LEN: ring_fwd_spec_head<LEN, T>(d, Fp, a, buf, syn); break;
+    case LEN: ring_fwd_spec_head<LEN, T, SHM>(d, Fp, a, buf); break;
         PAT_CFFT_LENGTHS_LO(PAT_RING_FWD_HEAD)
         default:
             if constexpr (G >= 1) {
@@ -268,8 +287,8 @@ __device__ __forceinline__ void ring_fwd_spec_tile(const PlanDev& d, const WsLay
             break;
 #undef PAT_RING_FWD_HEAD
     }
-    cfft_run_wg<true, G, T>(syn, d.fold_P >> 1, d.ctw + d.syn_ctw);
-    ring_fwd_spec_tail<T>(d, syn, hT + (size_t)n * d.D);
+    cfft_run_wg<true, G, T>(buf, d.fold_P >> 1, d.ctw + d.syn_ctw);
+    ring_fwd_spec_tail<T>(d, buf, hT + (size_t)n * d.D);
 }
 
 __global__ __launch_bounds__(kRingMaxThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_fwd(PlanDev d, WsLayout L, InstPtrs wsp, int RT, int batch)
@@ -324,10 +343,28 @@ void ring_fwd_launch(const pat_plan* p, const InstPtrs& wsp, int batch, hipStrea
     else hipLaunchKernelGGL(k_ring_fwd, grid, blk, p->lds_ring, st, d, p->ws, wsp, p->cfg.ring_rt, batch);
 }
 
-// The ring kernel of a heterogeneous batch of `items` work items.
-void ring_fwd_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, hipStream_t st)
+// Heterogeneous batches whose instances all have compile-time transforms: one
+// ring per workgroup of the largest instance's length group, without the
+// run-time form's registers and workgroup size.
+template <int G>
+__global__ __launch_bounds__(ring_spec_threads(G)) __attribute__((amdgpu_waves_per_eu(4))) void k_ring_fwd_spec_b(BatchDev bt, char* ws)
 {
-    hipLaunchKernelGGL(k_ring_fwd_b, dim3(xcd_grid(items)), dim3(threads), lds, st, bt, ws);
+    extern __shared__ float2 sm[];
+    int i, tile;
+    if (!batch_item(bt, kStRing, i, tile)) return;
+    const BatchInst& I = bt.inst[i];
+    const PlanDev d = I.d;
+    ring_fwd_spec_tile<G, 1>(d, I.L, ws + I.ws_off, d.nlam - 1 - tile, sm);  // largest rings first
+}
+
+// The ring kernel of a heterogeneous batch of `items` work items.
+void ring_fwd_b_launch(const BatchDev& bt, char* ws, int items, unsigned threads, size_t lds, int spec_grp, hipStream_t st)
+{
+    const dim3 grid(xcd_grid(items));
+    if (spec_grp == 0) hipLaunchKernelGGL(k_ring_fwd_spec_b<0>, grid, dim3(ring_spec_threads(0)), lds, st, bt, ws);
+    else if (spec_grp == 1) hipLaunchKernelGGL(k_ring_fwd_spec_b<1>, grid, dim3(ring_spec_threads(1)), lds, st, bt, ws);
+    else if (spec_grp == 2) hipLaunchKernelGGL(k_ring_fwd_spec_b<2>, grid, dim3(ring_spec_threads(2)), lds, st, bt, ws);
+    else hipLaunchKernelGGL(k_ring_fwd_b, grid, dim3(threads), lds, st, bt, ws);
 }
 
 }  // namespace pat
