@@ -626,12 +626,13 @@ extern "C" int pat_batch_create(pat_plan* const* plans, int count, pat_batch** o
         I.n_pair_tiles = p->n_pair_tiles;
     }
     b->ws_bytes = off;
-    // wide interpolation and spread tiles unless the batch is small
+    // the shapes single plans take for launches of this size (choose_launch)
     long cells = 0;
-    for (int i = 0; i < count; ++i) cells += (long)b->inst[i].d.Ng * b->inst[i].d.Hy;
+    for (int i = 0; i < count; ++i) cells += (long)b->inst[i].d.Ng * b->inst[i].d.NB;
     b->gat_cb = 64;
-    b->gat_th = 8;
-    if (cells >= 8L * 512 * 265) { b->gat_cb = 128; b->gat_th = 16; b->spr_cb = 256; }
+    b->gat_th = 16;
+    while (b->gat_th > 2 && cells / (64 * b->gat_th) < 8 * 256) b->gat_th /= 2;
+    b->spr_cb = 64;
     batch_layout(b);
     b->base_off = (sizeof(BatchInst) * (size_t)count + 255) & ~(size_t)255;
     int cur = 0;

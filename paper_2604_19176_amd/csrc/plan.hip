@@ -556,9 +556,24 @@ int apply_launch(pat_plan* p, const LaunchCfg& c)
     return PAT_OK;
 }
 
-// Default launch shapes: FFT tiles of <= 64 KB of LDS where possible (several
-// workgroups per CU; a single sequence may use up to 160 KB), interpolation
-// and spread tiles sized for `max_batch` instances.
+// Default launch shapes for calls of max_batch instances.  The rules come from
+// per-kernel timings at 32^2 .. 1024^2, batch 1 .. 64 (us, in the order of the choices):
+//   column passes: the most pairs (8, 4, 2: 16 NP bytes of a row side by side) that
+//     leave a workgroup per compute unit, never fewer than 2: 1024^2 batch 8 forward /
+//     adjoint 44 / 47 at 8 pairs, 55 / 73 at 3; 256^2 one image 8.3 / 8.2 at 2, 9.9 / 9.0 at 8;
+//   row passes: waves of a workgroup share nothing, so small workgroups: 1024^2 batch 8
+//     38 / 67 at 1 row, 53 / 82 at 8;
+//   cosine transform: 2 pairs, 1 for few detectors (256^2 batch 64 45.6 / 46.3 at 2, 53.5 / 57.7
+//     at 3, where a workgroup's waves leave a SIMD short);
+//   two waves per short ring where a launch has few rings (256^2 one image 10.7 / 11.0 -> 10.1 /
+//     10.1; batch 64 52.9 -> 67.9);
+//   interpolation: one instance per tile (a tile's windows for more instances cost more
+//     occupancy than the shared weights give: 256^2 batch 64 97 against 122 at four, 1024^2
+//     batch 8 168 against 236), the tallest tiles that still fill the chip (256^2 one image 9.1
+//     at 2 bands, 12.9 at 8);
+//   spread: four instances per tile, whose weights are the larger part of its staging (256^2
+//     batch 64 107 against 127 at two), 64 columns, 192 on wide grids (107 against 121 at 256;
+//     1024^2 187 against 209 at 128).
 int choose_launch(pat_plan* p, const std::vector<FftDev>& fd, int max_batch)
 {
     const PlanDev& d = p->dev;
@@ -575,21 +590,24 @@ int choose_launch(pat_plan* p, const std::vector<FftDev>& fd, int max_batch)
         if (v * bytes_each + fixed <= kLds && v * tps <= 1024) return v;
         return (bytes_each + fixed <= kLdsMax && tps <= 1024) ? 1 : 0;
     };
-    c.col_np = pick(8, sizeof(float2) * d.Ng, fg, twb_bytes(fg));
-    c.row_rpb = pick(8, sizeof(float2) * d.Ng, fg, twb_bytes(fg));
-    c.dct_dp = pick(4, sizeof(float2) * 2 * d.M, fm, twb_bytes(fm));
-    c.ring_rt = 1;
-    // wide tiles amortise the per-band work; narrow ones keep small batches parallel
-    const long gwide = (long)((d.Ng + 255) / 256) * ((d.NB + 31) / 32) * max_batch;
+    const long kCus = 256;
+    const long nb = max_batch, pairs = (d.N + 1) / 2, dpairs = (d.D + 1) / 2;
+    if (d.grid_spec) {
+        c.col_np = 8;
+        while (c.col_np > 2 && (pairs + c.col_np - 1) / c.col_np * nb < kCus) c.col_np /= 2;
+        c.row_rpb = d.Hy * nb >= 4 * kCus ? 2 : 1;
+    } else {
+        c.col_np = pick(8, sizeof(float2) * d.Ng, fg, twb_bytes(fg));
+        c.row_rpb = pick(8, sizeof(float2) * d.Ng, fg, twb_bytes(fg));
+    }
+    c.dct_dp = std::min(pick(4, sizeof(float2) * 2 * d.M, fm, twb_bytes(fm)), dpairs * nb >= 4 * kCus ? 2 : 1);
+    c.ring_rt = d.ring_spec && d.ring_spec_grp == 0 && d.nlam * nb <= 4 * kCus ? 2 : 1;
     c.gat_cb = 64;
-    c.gat_th = gwide >= 512 ? 16 : 8;
-    // spread: wide tiles for large batches, 128 columns for small ones (measured
-    // at 256^2: batch 1 fastest with 128..256 columns, 64 slower)
-    const int ib = tile_ib(4, max_batch);
-    c.gat_ib = ib;
-    c.spr_ib = ib;
-    const long groups = (max_batch + ib - 1) / ib;
-    c.spr_cb = (d.Ng >= 512 && groups >= 8) ? 256 : (d.Ng >= 256 ? 128 : 64);
+    c.gat_th = 16;
+    while (c.gat_th > 2 && (long)((d.Ng + 63) / 64) * ((d.NB + c.gat_th - 1) / c.gat_th) * nb < 8 * kCus) c.gat_th /= 2;
+    c.gat_ib = 1;
+    c.spr_ib = tile_ib(4, max_batch);
+    c.spr_cb = d.Ng >= 1024 ? 192 : 64;
     c.spr_th = kSpreadTh;
     if (!c.col_np || !c.row_rpb || !c.dct_dp) return PAT_ERR_UNSUPPORTED;
     return apply_launch(p, c);
