@@ -15,6 +15,8 @@
 // FP32), keeping only the box rows the detectors' stencils read; the inverse
 // transform along x of those rows; the Keys samples at the detectors.
 #include "../../include/pat.h"
+#include "cfft.hpp"
+#include "device_util.hpp"
 #include "fft.hpp"
 #include "pat_internal.hpp"
 
@@ -36,6 +38,12 @@ struct SimDev {
     const int2* mask_rows;  // [Ns]: image row i keeps columns jlo <= j < jhi (support disc)
     const int2* dix;        // [D]: box cell (x, y) of each detector's stencil sample at offset 0
     const float2* dfr;      // [D]: its fractional offsets (FP64-computed)
+    // compile-time box sides (cfft.hpp): only the box rows some stencil reads are kept
+    int nkeep;              // their number
+    const int* keep;        // [M]: index of a box row among them, or -1
+    const int* ent_ptr;     // [nkeep + 1]: the stencil rows that lie in each kept row
+    const int2* ent;        // (detector, stencil row 0 .. 3)
+    const float2* ctw;      // the length-M transform's table
     const float2* tw;       // twiddle table of the length-M transform
     FftDev fm;              // the length-M transform
 };
@@ -160,6 +168,131 @@ __global__ __launch_bounds__(1024) void k_sim_rows_inv(SimDev s, float2* __restr
     for (int e = threadIdx.x; e < nr * M; e += blockDim.x) base[e] = sm[e];
 }
 
+// ---------------------------------------------------------------------------
+// Compile-time box sides M (the even 2^a 3^b of 32 .. 2048).  Bound by VALU work per
+// box cell and pair of samples (the phase, its cosine, the transform); at a 1152^2
+// box, per 16 pairs, the run-time forms below take 149 us (columns) and 52 us
+// (rows), these 95 and 41; the arithmetic alone would take half of the 95:
+//   - rows r and M - r of a column share |k| and so the cosines, which are computed
+//     once and handed over in LDS;
+//   - cos(2 pi x) = sin(2 pi (|x - 1/2| - 1/4)) by one odd polynomial;
+//   - memory goes straight into the first pass and out of the last one;
+//   - only the rows some stencil reads leave the column transforms, and the row
+//     transforms keep just their samples (x weights applied), not the rows.
+// Sequences of kSimNP neighbouring columns (or rows) are interleaved over the
+// workgroup's threads, sim_lanes(M) lanes each (16 values per lane and pass).
+// ---------------------------------------------------------------------------
+constexpr int kSimNP = 8;
+__host__ __device__ constexpr int sim_lanes(int m) { return (m + 15) / 16; }
+constexpr int sim_threads(int m) { return (kSimNP * sim_lanes(m) + 63) / 64 * 64; }
+
+// alpha sqrt(q) as u_hi + u_lo for q = mx^2 + my^2 (exact in two floats); see sim_phase_frac
+__device__ __forceinline__ float2 sim_phase_rate(int mx, int my, float a_hi, float a_lo)
+{
+    const unsigned q = (unsigned)(mx * mx + my * my);
+    const float q_hi = (float)q;
+    const float q_lo = (float)(int)(q - (unsigned)q_hi);
+    const float s = __builtin_amdgcn_sqrtf(q_hi);
+    const float e = fmaf(-s, s, q_hi) + q_lo;
+    const float sc = q == 0u ? 0.f : e * __builtin_amdgcn_rcpf(2.f * s);
+    const float p = a_hi * s;
+    const float t = fmaf(a_hi, s, -p) + fmaf(a_hi, sc, a_lo * s);
+    const float u_hi = p + t;
+    return make_float2(u_hi, t - (u_hi - p));
+}
+
+// cos(2 pi j (u_hi + u_lo)): the product split exactly, its fraction, and the
+// Taylor polynomial of sin(2 pi u) on |u| <= 1/4 (degree 13: 7e-10)
+__device__ __forceinline__ float sim_cos(float J, float2 u)
+{
+    const float P = J * u.x;
+    const float L = fmaf(J, u.x, -P) + J * u.y;
+    const float x = __builtin_amdgcn_fractf(__builtin_amdgcn_fractf(P) + L);
+    const float v = fabsf(x - 0.5f) - 0.25f, w = v * v;
+    constexpr double t = 6.283185307179586476925;
+    constexpr double t3 = t * t * t, t5 = t3 * t * t, t7 = t5 * t * t, t9 = t7 * t * t, t11 = t9 * t * t, t13 = t11 * t * t;
+    float r = (float)(t13 / 6227020800.0);
+    r = fmaf(r, w, (float)(-t11 / 39916800.0));
+    r = fmaf(r, w, (float)(t9 / 362880.0));
+    r = fmaf(r, w, (float)(-t7 / 5040.0));
+    r = fmaf(r, w, (float)(t5 / 120.0));
+    r = fmaf(r, w, (float)(-t3 / 6.0));
+    // the leading term with 2 pi in two floats: its rounding would show in every value
+    constexpr float th = (float)t, tl = (float)(t - (double)(float)t);
+    return fmaf(th, v, fmaf(tl, v, r * w * v));
+}
+
+// Pair p of the chunk: the inverse FFT along y of F (cos(c|k|t_a) + i cos(c|k|t_b))
+// -> kept rows Wt [chunk][nkeep][M].  Column tile by column tile, its pairs in
+// turn, tiles contiguous per XCD: a tile's 64 bytes of F's rows stay cached from
+// pair to pair, and the two tiles of a 128-byte line share an L2.
+template <int M>
+__global__ __launch_bounds__(sim_threads(M)) void k_sim_cols_inv_spec(SimDev s, const float2* __restrict__ F,
+                                                                      float2* __restrict__ Wt, int pair0, int npairs)
+{
+    extern __shared__ __align__(16) float2 sm[];
+    constexpr int T = sim_lanes(M), LD = grid_col_ld(M);
+    using Fst = cfft_first<M, T>;
+    constexpr int RH = (Fst::R + 1) / 2;  // inputs r < RH of a lane: rows up to the middle
+    const int item = xcd_item(blockIdx.x, (M + kSimNP - 1) / kSimNP * npairs);
+    if (item < 0) return;
+    const int tile = item / npairs, p = item - tile * npairs;
+    const int lane = threadIdx.x / kSimNP, sq = threadIdx.x % kSimNP;
+    const int c = tile * kSimNP + sq, mx = c < M / 2 ? c : c - M;
+    const bool on = lane < T && c < M;
+    const int ja = 2 * (pair0 + p) + 1;
+    const bool has_b = ja + 1 <= s.T;
+    float2* x = sm + sq * LD;
+    float2* out = Wt + (size_t)p * s.nkeep * M + c;
+    auto cosines = [&](int row) {  // rows up to M / 2
+        const float2 u = sim_phase_rate(mx, row, s.a_hi, s.a_lo);
+        return make_float2(sim_cos((float)ja, u), has_b ? sim_cos((float)(ja + 1), u) : 0.f);
+    };
+    // rows r and M - r share their cosines: the lower half is computed and
+    // handed over in LDS, ahead of the transform
+    float2 cs[Fst::RND][Fst::R];
+    if (on) {
+#pragma unroll
+        for (int i = 0; i < Fst::RND; ++i)
+#pragma unroll
+            for (int r = 0; r < RH; ++r) {
+                const int row = Fst::pos(lane, i, r);
+                cs[i][r] = cosines(row <= M / 2 ? row : M - row);
+                x[cfft_slot<true>(row)] = cs[i][r];
+            }
+    }
+    __syncthreads();
+    if (on) {
+#pragma unroll
+        for (int i = 0; i < Fst::RND; ++i)
+#pragma unroll
+            for (int r = RH; r < Fst::R; ++r) {
+                const int row = Fst::pos(lane, i, r);
+                cs[i][r] = 2 * row == M ? cosines(row) : x[cfft_slot<true>(M - row)];
+            }
+    }
+    __syncthreads();
+    cfft_stream<M, true, T, SyncWg, false>(
+        x, s.ctw, on, lane,
+        [&](float2 (&v)[Fst::RND][Fst::R]) {
+#pragma unroll
+            for (int i = 0; i < Fst::RND; ++i)
+#pragma unroll
+                for (int r = 0; r < Fst::R; ++r) v[i][r] = F[(size_t)Fst::pos(lane, i, r) * M + c];
+#pragma unroll
+            for (int i = 0; i < Fst::RND; ++i)
+#pragma unroll
+                for (int r = 0; r < Fst::R; ++r) {
+                    const float2 z = v[i][r], k = cs[i][r];
+                    v[i][r] = make_float2(z.x * k.x - z.y * k.y, z.y * k.x + z.x * k.y);
+                }
+        },
+        [&](int pos, float2 z) {
+            const int row = s.keep[pos];
+            if (row >= 0) out[(size_t)row * M] = z;
+        });
+}
+
 // Keys cubic convolution weight (a = -1/2) at distance t (0 <= t < 2)
 __device__ __forceinline__ float keys_w(float t)
 {
@@ -167,6 +300,70 @@ __device__ __forceinline__ float keys_w(float t)
     return t <= 1.f ? ((a + 2.f) * t - (a + 3.f)) * t * t + 1.f : ((a * t - 5.f * a) * t + 8.f * a) * t - 4.f * a;
 }
 
+// Inverse FFT along x of kept rows; their stencil rows' samples -> S [chunk][D][4]
+template <int M>
+__global__ __launch_bounds__(sim_threads(M)) void k_sim_rows_inv_spec(SimDev s, const float2* __restrict__ Wt,
+                                                                      float2* __restrict__ S)
+{
+    extern __shared__ __align__(16) float2 sm[];
+    constexpr int T = sim_lanes(M), LD = grid_col_ld(M);
+    using Fst = cfft_first<M, T>;
+    const int p = blockIdx.y, lane = threadIdx.x / kSimNP, sq = threadIdx.x % kSimNP;
+    const int r0 = blockIdx.x * kSimNP, row = r0 + sq;
+    const float2* src = Wt + ((size_t)p * s.nkeep + min(row, s.nkeep - 1)) * M;
+    float2* x = sm + sq * LD;
+    cfft_stream<M, true, T, SyncWg, true>(
+        x, s.ctw, lane < T && row < s.nkeep, lane,
+        [&](float2 (&v)[Fst::RND][Fst::R]) {
+#pragma unroll
+            for (int i = 0; i < Fst::RND; ++i)
+#pragma unroll
+                for (int r = 0; r < Fst::R; ++r) v[i][r] = src[Fst::pos(lane, i, r)];
+        },
+        [&](int pos, float2 z) { x[cfft_slot<true>(pos)] = z; });
+    for (int k = 0; k < kSimNP && r0 + k < s.nkeep; ++k)
+        for (int e = s.ent_ptr[r0 + k] + threadIdx.x; e < s.ent_ptr[r0 + k + 1]; e += blockDim.x) {
+            const int2 en = s.ent[e];
+            const int ix = s.dix[en.x].x;
+            const float fx = s.dfr[en.x].x;
+            const float wx[4] = {keys_w(1.f + fx), keys_w(fx), keys_w(1.f - fx), keys_w(2.f - fx)};
+            const float2* rowp = sm + k * LD;
+            float2 ra = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const float2 v = rowp[cfft_slot<true>(ix - 1 + b)];
+                ra.x = fmaf(wx[b], v.x, ra.x);
+                ra.y = fmaf(wx[b], v.y, ra.y);
+            }
+            S[((size_t)p * s.D + en.x) * 4 + en.y] = ra;
+        }
+}
+
+// The stencil rows' sum at each detector: thread (d, p) -> g[d][ja - 1] and g[d][jb - 1]
+__global__ __launch_bounds__(256) void k_sim_combine(SimDev s, const float2* __restrict__ S, float* __restrict__ g, int pair0,
+                                                     int npairs)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= s.D * npairs) return;
+    const int d = t / npairs, p = t - d * npairs;
+    const int ja = 2 * (pair0 + p) + 1, jb = ja + 1;
+    const float fy = s.dfr[d].y;
+    const float wy[4] = {keys_w(1.f + fy), keys_w(fy), keys_w(1.f - fy), keys_w(2.f - fy)};
+    float2 acc = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const float2 ra = S[((size_t)p * s.D + d) * 4 + a];
+        acc.x = fmaf(wy[a], ra.x, acc.x);
+        acc.y = fmaf(wy[a], ra.y, acc.y);
+    }
+    const float scale = 1.0f / ((float)s.M * (float)s.M);
+    g[(size_t)d * s.T + ja - 1] = acc.x * scale;
+    if (jb <= s.T) g[(size_t)d * s.T + jb - 1] = acc.y * scale;
+}
+
+// ---------------------------------------------------------------------------
+// Run-time box sides (above 2048)
+// ---------------------------------------------------------------------------
 // Samples at the detectors: thread (d, p) -> g[d][ja - 1] and g[d][jb - 1]
 __global__ __launch_bounds__(256) void k_sim_sample(SimDev s, const float2* __restrict__ Wt, float* __restrict__ g,
                                                     int pair0, int npairs)
@@ -213,7 +410,8 @@ struct pat_sim {
     int thr_col, thr_row;       // workgroup sizes of the column and row transforms
     size_t lds_col, lds_row;    // their dynamic LDS
     int npairs, chunk;          // time-sample pairs, pairs per chunk
-    size_t off_F, off_W, off_Wt, ws_bytes;
+    size_t off_F, off_W, off_Wt, off_S, ws_bytes;
+    int spec;                   // compile-time box side
 };
 
 namespace {
@@ -337,14 +535,48 @@ extern "C" int pat_sim_create(const pat_plan_desc* desc, pat_sim** out)
         return PAT_ERR_UNSUPPORTED;
     }
 
+    // compile-time box sides: the kept rows, the stencil rows in each, the transform's table
+    s->spec = pat::grid_len_ok(M);
+    std::vector<int> keep(M, -1), eptr;
+    std::vector<int2> ent;
+    std::vector<float2> ctw;
+    if (s->spec) {
+        std::vector<std::vector<int2>> in_row(M);
+        for (int q = 0; q < D; ++q)
+            for (int a = 0; a < 4; ++a) in_row[dix[q].y - 1 + a].push_back(make_int2(q, a));
+        for (int r = 0; r < M; ++r) {
+            if (in_row[r].empty()) continue;
+            keep[r] = d.nkeep++;
+            eptr.push_back((int)ent.size());
+            ent.insert(ent.end(), in_row[r].begin(), in_row[r].end());
+        }
+        eptr.push_back((int)ent.size());
+        const pat::CPlan cp = pat::make_cplan(M);
+        ctw.resize(cp.twoff[cp.np]);
+        for (int st = 0; st < cp.np; ++st)
+            for (int k = 0; cp.ns[st] > 1 && k < cp.ns[st]; ++k)
+                for (int r = 1; r < cp.rad[st]; ++r) {
+                    const double a = -2.0 * 3.14159265358979323846 * (double)(k * r) / (double)(cp.ns[st] * cp.rad[st]);
+                    ctw[cp.twoff[st] + k * (cp.rad[st] - 1) + r - 1] = make_float2((float)std::cos(a), (float)std::sin(a));
+                }
+    }
+
     // device tables
     size_t o_mask = 0, o_dix = align256(o_mask + sizeof(int2) * Ns), o_dfr = align256(o_dix + sizeof(int2) * D),
-           o_tw = align256(o_dfr + sizeof(float2) * D), bytes = o_tw + sizeof(float2) * tw.size();
+           o_tw = align256(o_dfr + sizeof(float2) * D), o_keep = align256(o_tw + sizeof(float2) * tw.size()),
+           o_eptr = align256(o_keep + sizeof(int) * keep.size()), o_ent = align256(o_eptr + sizeof(int) * eptr.size()),
+           o_ctw = align256(o_ent + sizeof(int2) * ent.size()), bytes = o_ctw + sizeof(float2) * ctw.size();
     std::vector<unsigned char> host(bytes, 0);
     std::memcpy(host.data() + o_mask, mrows.data(), sizeof(int2) * Ns);
     std::memcpy(host.data() + o_dix, dix.data(), sizeof(int2) * D);
     std::memcpy(host.data() + o_dfr, dfr.data(), sizeof(float2) * D);
     std::memcpy(host.data() + o_tw, tw.data(), sizeof(float2) * tw.size());
+    std::memcpy(host.data() + o_keep, keep.data(), sizeof(int) * keep.size());
+    if (s->spec) {
+        std::memcpy(host.data() + o_eptr, eptr.data(), sizeof(int) * eptr.size());
+        std::memcpy(host.data() + o_ent, ent.data(), sizeof(int2) * ent.size());
+        std::memcpy(host.data() + o_ctw, ctw.data(), sizeof(float2) * ctw.size());
+    }
     if (hipGetDevice(&s->device) != hipSuccess) {
         delete s;
         return PAT_ERR_HIP;
@@ -363,6 +595,10 @@ extern "C" int pat_sim_create(const pat_plan_desc* desc, pat_sim** out)
     d.dix = (const int2*)(base + o_dix);
     d.dfr = (const float2*)(base + o_dfr);
     d.tw = (const float2*)(base + o_tw);
+    d.keep = (const int*)(base + o_keep);
+    d.ent_ptr = (const int*)(base + o_eptr);
+    d.ent = (const int2*)(base + o_ent);
+    d.ctw = (const float2*)(base + o_ctw);
 
     // workspace: F [M][M], W [Ns][M], Wt [chunk][nrow][M]
     s->npairs = (T + 1) / 2;
@@ -371,6 +607,14 @@ extern "C" int pat_sim_create(const pat_plan_desc* desc, pat_sim** out)
     s->off_W = align256(sizeof(float2) * (size_t)M * M);
     s->off_Wt = s->off_W + align256(sizeof(float2) * (size_t)Ns * M);
     s->ws_bytes = s->off_Wt + align256(sizeof(float2) * (size_t)s->chunk * d.nrow * M);
+    // compile-time box sides: the stencil rows' samples [chunk][D][4], over W
+    // (read before the first of them is written) where they fit
+    const size_t s_bytes = align256(sizeof(float2) * 4 * (size_t)s->chunk * D);
+    s->off_S = s->off_W;
+    if (s->spec && s_bytes > s->off_Wt - s->off_W) {
+        s->off_S = s->ws_bytes;
+        s->ws_bytes += s_bytes;
+    }
     *out = s;
     return PAT_OK;
 }
@@ -399,8 +643,29 @@ extern "C" int pat_sim_run(const pat_sim* s, const float* f, float* g, void* ws,
     hipLaunchKernelGGL(pat::k_sim_cols_fwd, dim3((d.M + d.CT - 1) / d.CT), dim3(s->thr_col), s->lds_col, st, d,
                        (const float2*)W, F);
     if (hipGetLastError() != hipSuccess) return PAT_ERR_HIP;
+    float2* Sd = (float2*)(w + s->off_S);
     for (int p0 = 0; p0 < s->npairs; p0 += s->chunk) {
         const int np = std::min(s->chunk, s->npairs - p0);
+        if (s->spec) {
+            const dim3 gc(pat::xcd_grid((d.M + pat::kSimNP - 1) / pat::kSimNP * np)), gr((d.nkeep + pat::kSimNP - 1) / pat::kSimNP, np);
+            switch (d.M) {
+#define PAT_CASE(LEN)                                                                                                 \
+    case LEN: {                                                                                                       \
+        const size_t lds = sizeof(float2) * (size_t)pat::kSimNP * pat::grid_col_ld(LEN);                               \
+        hipLaunchKernelGGL(pat::k_sim_cols_inv_spec<LEN>, gc, dim3(pat::sim_threads(LEN)), lds, st, d, (const float2*)F, Wt, p0, np); \
+        hipLaunchKernelGGL(pat::k_sim_rows_inv_spec<LEN>, gr, dim3(pat::sim_threads(LEN)), lds, st, d, (const float2*)Wt, Sd);    \
+        break;                                                                                                        \
+    }
+                PAT_GRID_LENGTHS(PAT_CASE)
+#undef PAT_CASE
+                default: break;
+            }
+            if (hipGetLastError() != hipSuccess) return PAT_ERR_HIP;
+            hipLaunchKernelGGL(pat::k_sim_combine, dim3((d.D * np + 255) / 256), dim3(256), 0, st, d, (const float2*)Sd, g,
+                               p0, np);
+            if (hipGetLastError() != hipSuccess) return PAT_ERR_HIP;
+            continue;
+        }
         hipLaunchKernelGGL(pat::k_sim_cols_inv, dim3((d.M + d.CT - 1) / d.CT, np), dim3(s->thr_col), s->lds_col, st, d,
                            (const float2*)F, Wt, p0);
         if (hipGetLastError() != hipSuccess) return PAT_ERR_HIP;
