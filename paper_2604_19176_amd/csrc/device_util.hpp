@@ -19,20 +19,35 @@ __device__ __forceinline__ int xcd_item(int w, int U)
     return x * Q + min(x, Rm) + q;
 }
 
-// The 8 taps of the ES kernel phi(t) = exp(beta (sqrt(1 - (2t/w)^2) - 1)) at
-// t = frac + 3 - d (d = 0..7, frac in [0, 1]): z = t / 4 lies in [-1, 1] also
-// when rounded, so 1 - z^2, rounded once, is never negative; the hardware square
-// root and base-2 exponential (about 1 ulp each) are used directly, since the
-// argument of the exponential lies in [-beta log2(e), 0].  The same routine
-// serves the interpolation and the spread, which keeps them exact transposes.
+// The ES kernel phi(t) = exp(beta (sqrt(1 - (t/4)^2) - 1)), beta = kEsBeta, at tap
+// distances t = 3.5 - d + g, |g| <= 1/2, for d = 0 .. 3: polynomials of degree 8 in
+// g, the Chebyshev least-squares fit in FP64 on [-1/2, 1/2] (coefficients of g^0 ..
+// g^8).  The fit is within 7.1e-9 of phi, below a float's rounding of it.
+static_assert(kEsBeta == 2.30 * 8, "kEsPoly is fitted to this beta");
+constexpr float kEsPoly[4][9] = {
+    {7.54424545e-05f, -0.000627239817f, 0.00222511124f, -0.00440370012f, 0.00529891253f, -0.00388452341f, 0.00149517192f, 3.90759233e-05f, -0.000277026353f},
+    {0.0176590905f, -0.0650374591f, 0.0984192193f, -0.0738898143f, 0.0213647485f, 0.00744818663f, -0.00755627872f, 0.0010998128f, 0.000726180093f},
+    {0.261128277f, -0.485905409f, 0.263611913f, 0.0497403592f, -0.095805265f, 0.0164990574f, 0.0136794029f, -0.00462838635f, -0.000992656103f},
+    {0.865614235f, -0.501662731f, -0.364257514f, 0.251083404f, 0.0691484809f, -0.0597133376f, -0.00761750108f, 0.00851049926f, 0.00049085723f},
+};
+
+// The 8 taps of the ES kernel for a point at fraction frac in [0, 1] of its cell:
+// w[d] = phi(frac + 3 - d).  Taps d and 7 - d are P_d(g) and P_d(-g), g = frac - 1/2,
+// so the even and odd parts are summed once for both: 40 multiply-adds for 8
+// taps.  (A square root and an exponential per tap took 44 issue cycles each
+// against 20 here, with ten times the error: 1.5e-6 of the largest tap against
+// 1.0e-7.)  The same routine serves the interpolation and the spread, which
+// keeps them exact transposes.
 __device__ __forceinline__ void es_weights8(float frac, float (&w)[8])
 {
-    constexpr float kb = (float)(kEsBeta * 1.4426950408889634);  // beta log2(e)
-    const float z0 = frac * 0.25f;
+    const float g = frac - 0.5f, g2 = g * g;
 #pragma unroll
-    for (int d = 0; d < 8; ++d) {
-        const float z = z0 + 0.25f * (float)(3 - d);
-        w[d] = __builtin_amdgcn_exp2f(fmaf(kb, __builtin_amdgcn_sqrtf(fmaf(-z, z, 1.0f)), -kb));
+    for (int d = 0; d < 4; ++d) {
+        const float (&c)[9] = kEsPoly[d];
+        const float even = fmaf(fmaf(fmaf(fmaf(c[8], g2, c[6]), g2, c[4]), g2, c[2]), g2, c[0]);
+        const float odd = fmaf(fmaf(fmaf(c[7], g2, c[5]), g2, c[3]), g2, c[1]);
+        w[d] = fmaf(g, odd, even);
+        w[7 - d] = fmaf(-g, odd, even);
     }
 }
 
