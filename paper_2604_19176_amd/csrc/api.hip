@@ -313,7 +313,7 @@ extern "C" int pat_tv_grad(const float* f, float* grad, float* tv, int n, int ba
 {
     if (!f || !grad || n < 2 || batch < 1 || !(eps > 0.f)) return PAT_ERR_ARG;
     hipStream_t st = (hipStream_t)stream;
-    dim3 grid((n + 15) / 16, (n + 15) / 16, batch);
+    dim3 grid((n + kTvCols - 1) / kTvCols, (n + 4 * kTvRows - 1) / (4 * kTvRows), batch);
     hipLaunchKernelGGL(k_tv_grad, grid, dim3(256), 0, st, f, grad, n, eps * eps);
     int rc = check_launch();
     if (rc || !tv) return rc;
@@ -356,7 +356,7 @@ extern "C" int pat_pd_dual_data(float* y1, const float* ax, const float* g, long
 extern "C" int pat_pd_dual_tv(float* y2, const float* xbar, int n, int batch, float sigma, float alpha, void* stream)
 {
     if (!y2 || !xbar || n < 2 || batch < 1 || !(sigma > 0.f) || !(alpha >= 0.f)) return PAT_ERR_ARG;
-    const dim3 grid((n + 15) / 16, (n + 15) / 16, batch);
+    const dim3 grid((n + 63) / 64, (n + 3) / 4, batch);
     hipLaunchKernelGGL(k_pd_dual_tv, grid, dim3(256), 0, (hipStream_t)stream, (float2*)y2, xbar, n, sigma, alpha);
     return check_launch();
 }
@@ -365,7 +365,7 @@ extern "C" int pat_pd_primal(float* f, float* xbar, const float* aty, const floa
                              void* stream)
 {
     if (!f || !xbar || !aty || !y2 || n < 2 || batch < 1 || !(tau > 0.f)) return PAT_ERR_ARG;
-    const dim3 grid((n + 15) / 16, (n + 15) / 16, batch);
+    const dim3 grid((n + 63) / 64, (n + 3) / 4, batch);
     hipLaunchKernelGGL(k_pd_primal, grid, dim3(256), 0, (hipStream_t)stream, f, xbar, aty, (const float2*)y2, n,
                        tau);
     return check_launch();

@@ -43,6 +43,25 @@ __device__ float block_sum(float v, float* scratch)
     return r;
 }
 
+// Sum of term(e), e < n, over the workgroup's threads, each in order (eight
+// loads in flight: one workgroup reduces an image, so it is bound by their latency)
+template <class Term>
+__device__ __forceinline__ float strided_sum(long n, Term term)
+{
+    float acc = 0.f;
+    const long bd = blockDim.x;
+    long e = threadIdx.x;
+    for (; e + 7 * bd < n; e += 8 * bd) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = term(e + u * bd);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += v[u];
+    }
+    for (; e < n; e += bd) acc += term(e);
+    return acc;
+}
+
 // Row / sample classes of the endpoint-term sums; red_s[1024] holds
 // kSumClasses x (columns or detectors of a tile), so tiles have at most 32 of
 // either (col_np, dct_dp <= 16).
@@ -1333,49 +1352,79 @@ __global__ __launch_bounds__(CB) void k_spread_b(BatchDev bt, char* ws)
 // ---------------------------------------------------------------------------
 // total variation (smoothed, isotropic, forward differences, Neumann boundary)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float tv_mag(const float* f, int n, int i, int j, float eps2, float& dx, float& dy)
-{
-    const float c = f[(size_t)i * n + j];
-    dx = (j + 1 < n) ? f[(size_t)i * n + j + 1] - c : 0.f;
-    dy = (i + 1 < n) ? f[(size_t)(i + 1) * n + j] - c : 0.f;
-    return sqrtf(dx * dx + dy * dy + eps2);
-}
-
+// A wave takes 62 columns (and one beside them on either side) and kTvRows rows:
+// its loads come first, neighbours' values and quotients from the lanes beside and
+// the row above, so that a pixel's root and divisions are done once (the kernel is
+// bound by them; three evaluations per pixel before).  1024^2, batch 8:
+// 48 -> 21 us.
+constexpr int kTvRows = 4, kTvCols = 62;
 __global__ __launch_bounds__(256) void k_tv_grad(const float* __restrict__ f, float* __restrict__ grad, int n,
                                                  float eps2)
 {
-    const int b = blockIdx.z;
-    const int j = blockIdx.x * 16 + (threadIdx.x & 15);
-    const int i = blockIdx.y * 16 + (threadIdx.x >> 4);
-    if (i >= n || j >= n) return;
+    const int b = blockIdx.z, lane = threadIdx.x & 63;
+    const int j = blockIdx.x * kTvCols + lane - 1;
+    const int i0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * kTvRows;
+    if (i0 >= n) return;
     const float* fb = f + (size_t)b * n * n;
-    float dx, dy;
-    const float s = tv_mag(fb, n, i, j, eps2, dx, dy);
-    float gval = -(dx + dy) / s;
-    if (j > 0) {
-        float dxl, dyl;
-        const float sl = tv_mag(fb, n, i, j - 1, eps2, dxl, dyl);
-        gval += dxl / sl;
+    float* gb = grad + (size_t)b * n * n;
+    const int jc = min(max(j, 0), n - 1);
+    float c[kTvRows + 2];  // rows i0 - 1 .. i0 + kTvRows
+#pragma unroll
+    for (int r = 0; r < kTvRows + 2; ++r) c[r] = fb[(size_t)min(max(i0 - 1 + r, 0), n - 1) * n + jc];
+    const bool out = lane > 0 && lane <= kTvCols && j < n;
+    float up = 0.f;  // dy / s of the row above
+#pragma unroll
+    for (int r = 0; r <= kTvRows; ++r) {
+        const int i = i0 - 1 + r;
+        const float right = __shfl_down(c[r], 1, 64);
+        const float dx = j + 1 < n ? right - c[r] : 0.f;
+        const float dy = i + 1 < n ? c[r + 1] - c[r] : 0.f;
+        const float s = sqrtf(dx * dx + dy * dy + eps2);
+        if (r > 0) {
+            const float left = __shfl_up(dx / s, 1, 64);
+            float gval = -(dx + dy) / s;
+            if (j > 0) gval += left;
+            if (i > 0) gval += up;
+            if (out && i < n) gb[(size_t)i * n + j] = gval;
+        }
+        up = dy / s;
     }
-    if (i > 0) {
-        float dxu, dyu;
-        const float su = tv_mag(fb, n, i - 1, j, eps2, dxu, dyu);
-        gval += dyu / su;
-    }
-    grad[(size_t)b * n * n + (size_t)i * n + j] = gval;
 }
 
+// One workgroup per image: a wave takes four rows and 128 columns at a time, so that
+// the latency of its loads, which bounds it, is paid once for 512 pixels.
+// 200^2, batch 5: 29 -> 14 us (a 64-bit division per pixel before).
 __global__ __launch_bounds__(1024) void k_tv_value(const float* __restrict__ f, float* __restrict__ tv, int n,
                                                    float eps2)
 {
     __shared__ float red_s[1024];
     const int b = blockIdx.x;
     const float* fb = f + (size_t)b * n * n;
+    const int lane = threadIdx.x & 63;
+    const int nx = (n + 127) / 128, items = nx * ((n + 3) / 4);
     float acc = 0.f;
-    for (long e = threadIdx.x; e < (long)n * n; e += blockDim.x) {
-        const int i = (int)(e / n), j = (int)(e - (long)i * n);
-        float dx, dy;
-        acc += tv_mag(fb, n, i, j, eps2, dx, dy);
+    for (int it = threadIdx.x >> 6; it < items; it += 16) {
+        const int q = it / nx, i = 4 * q, j0 = (it - q * nx) * 128 + lane;
+        float c[5][2], r[4][2];
+#pragma unroll
+        for (int u = 0; u < 5; ++u) {
+            const float* row = fb + (size_t)min(i + u, n - 1) * n;
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const int j = j0 + 64 * v;
+                c[u][v] = row[min(j, n - 1)];
+                if (u < 4) r[u][v] = row[min(j + 1, n - 1)];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const float dx = j0 + 64 * v + 1 < n ? r[u][v] - c[u][v] : 0.f;
+                const float dy = i + u + 1 < n ? c[u + 1][v] - c[u][v] : 0.f;
+                const float m = sqrtf(dx * dx + dy * dy + eps2);
+                acc += j0 + 64 * v < n && i + u < n ? m : 0.f;
+            }
     }
     const float tot = block_sum(acc, red_s);
     if (threadIdx.x == 0) tv[b] = tot;
@@ -1404,9 +1453,7 @@ __global__ __launch_bounds__(1024) void k_half_sq(const float* __restrict__ g, f
     __shared__ float red_s[1024];
     const int b = blockIdx.x;
     const float* gb = g + (size_t)b * per;
-    float acc = 0.f;
-    for (long e = threadIdx.x; e < per; e += blockDim.x) acc += gb[e] * gb[e];
-    const float tot = block_sum(acc, red_s);
+    const float tot = block_sum(strided_sum(per, [&](long e) { return gb[e] * gb[e]; }), red_s);
     if (threadIdx.x == 0) sq[b] = 0.5f * tot;
 }
 
@@ -1428,8 +1475,8 @@ __global__ __launch_bounds__(256) void k_pd_dual_tv(float2* __restrict__ y2, con
                                                     float sigma, float alpha)
 {
     const int b = blockIdx.z;
-    const int j = blockIdx.x * 16 + (threadIdx.x & 15);
-    const int i = blockIdx.y * 16 + (threadIdx.x >> 4);
+    const int j = blockIdx.x * 64 + (threadIdx.x & 63);  // a wave per row of 64 columns
+    const int i = blockIdx.y * 4 + (threadIdx.x >> 6);
     if (i >= n || j >= n) return;
     const float* xb = xbar + (size_t)b * n * n;
     const size_t e = (size_t)b * n * n + (size_t)i * n + j;
@@ -1450,8 +1497,8 @@ __global__ __launch_bounds__(256) void k_pd_primal(float* __restrict__ f, float*
                                                    int n, float tau)
 {
     const int b = blockIdx.z;
-    const int j = blockIdx.x * 16 + (threadIdx.x & 15);
-    const int i = blockIdx.y * 16 + (threadIdx.x >> 4);
+    const int j = blockIdx.x * 64 + (threadIdx.x & 63);  // a wave per row of 64 columns
+    const int i = blockIdx.y * 4 + (threadIdx.x >> 6);
     if (i >= n || j >= n) return;
     const size_t base = (size_t)b * n * n;
     const size_t e = base + (size_t)i * n + j;
@@ -1478,14 +1525,11 @@ __global__ __launch_bounds__(1024) void k_pd_change(const float* __restrict__ f,
     const int b = blockIdx.x;
     const float* fb = f + (size_t)b * per;
     const float* xb = xbar + (size_t)b * per;
-    float sd = 0.f, sf = 0.f;
-    for (long e = threadIdx.x; e < per; e += blockDim.x) {
-        const float v = fb[e], dlt = xb[e] - v;
-        sd += dlt * dlt;
-        sf += v * v;
-    }
-    const float td = block_sum(sd, red_s);
-    const float tf = block_sum(sf, red_s);
+    const float td = block_sum(strided_sum(per, [&](long e) {
+        const float dlt = xb[e] - fb[e];
+        return dlt * dlt;
+    }), red_s);
+    const float tf = block_sum(strided_sum(per, [&](long e) { return fb[e] * fb[e]; }), red_s);
     if (threadIdx.x == 0) {
         out[2 * b] = td;
         out[2 * b + 1] = tf;
@@ -1501,9 +1545,7 @@ __global__ __launch_bounds__(1024) void k_cg_norm2(const float* __restrict__ x, 
     __shared__ float red_s[1024];
     const int b = blockIdx.x;
     const float* xb = x + (size_t)b * per;
-    float acc = 0.f;
-    for (long e = threadIdx.x; e < per; e += blockDim.x) acc += xb[e] * xb[e];
-    const float t = block_sum(acc, red_s);
+    const float t = block_sum(strided_sum(per, [&](long e) { return xb[e] * xb[e]; }), red_s);
     if (threadIdx.x == 0) out[b] = t;
 }
 
