@@ -131,13 +131,9 @@ __device__ __forceinline__ float2 syn_prologue(float2 y1, float2 y1m, float2 y2,
     return make_float2(E.x - O.y, E.y + O.x);
 }
 
-// SHM: longest half-length synthesis of the length group.  The synthesis input
-// takes the place of the modes in buf (held in registers across the barrier):
-// one buffer of max(Npsi_max / 2, P / 2) values per ring keeps twice as many rings
-// resident.
-template <int Pn, int T, int SHM>
-__device__ __forceinline__ void ring_fwd_spec_head(const PlanDev& d, const float2* __restrict__ Fp,
-                                                   const RingSpecArgs& a, float2* buf)
+// The modes a_k of a ring of Pn values, in buf.
+template <int Pn, int T>
+__device__ __forceinline__ void ring_fwd_spec_head(const float2* __restrict__ Fp, const RingSpecArgs& a, float2* buf)
 {
     const int lane = threadIdx.x;
     const bool act = lane < T;
@@ -190,10 +186,23 @@ __device__ __forceinline__ void ring_fwd_spec_head(const PlanDev& d, const float
         }
     }
     __syncthreads();
+}
+
+// Folds the Pn modes in buf into the synthesis input, in their place (held in
+// registers across the barrier): one buffer of max(Npsi_max / 2, P / 2) values per
+// ring keeps twice as many rings resident.  SHM: longest half-length synthesis of
+// the length group.  Outside the dispatch on the ring's length: with a copy per
+// length the translation unit took 18 minutes to compile.
+template <int T, int SHM>
+__device__ __forceinline__ void ring_fwd_spec_fold(const PlanDev& d, int Pn, float2* buf)
+{
+    const int lane = threadIdx.x;
+    const bool act = lane < T;
     const int Pf = d.fold_P, SH = Pf >> 1;
     // y_q = sum of a_k over k = q mod Pf, k < Pn (a_k = 0 above K_n), in increasing k
     auto mode = [&](int q) {
         float2 y = q < Pn ? buf[q] : make_float2(0.f, 0.f);
+#pragma unroll 1
         for (int k = q + Pf; k < Pn; k += Pf) y = cadd(y, buf[k]);
         return y;
     };
@@ -268,7 +277,7 @@ __device__ __forceinline__ void ring_fwd_spec_tile(const PlanDev& d, const WsLay
     constexpr int T = ring_spec_threads(G, W), SHM = ring_spec_max(G);
     switch (Pn) {
 #define PAT_RING_FWD_HEAD(LEN) \
-    case LEN: ring_fwd_spec_head<LEN, T, SHM>(d, Fp, a, buf); break;
+    case LEN: ring_fwd_spec_head<LEN, T>(Fp, a, buf); break;
         PAT_CFFT_LENGTHS_LO(PAT_RING_FWD_HEAD)
         default:
             if constexpr (G >= 1) {
@@ -287,6 +296,7 @@ __device__ __forceinline__ void ring_fwd_spec_tile(const PlanDev& d, const WsLay
             break;
 #undef PAT_RING_FWD_HEAD
     }
+    ring_fwd_spec_fold<T, SHM>(d, Pn, buf);
     cfft_run_wg<true, G, T>(buf, d.fold_P >> 1, d.ctw + d.syn_ctw);
     ring_fwd_spec_tail<T>(d, buf, hT + (size_t)n * d.D);
 }
