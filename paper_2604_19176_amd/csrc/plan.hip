@@ -495,30 +495,40 @@ static size_t ring_lds_bytes(const PlanDev& d, int RT)
 
 constexpr size_t kLdsMax = 160 * 1024;  // LDS a gfx950 workgroup can hold
 
+// v sequences of one transform per workgroup fit: tiles of at most 16 pairs (the
+// endpoint-term sums take at most 32 columns or detectors), LDS and threads.
+static bool fft_shape_ok(int v, size_t each, const FftDev& f, size_t fixed)
+{
+    return v >= 1 && v <= 16 && v * each + fixed <= kLdsMax && fft_threads(v, f) <= 1024;
+}
+
+// The 2D-FFT shapes (col_np, row_rpb) a plan takes.  Other than powers of two they
+// are held to the run-time transform's threads on every grid side, also where the
+// compile-time passes would run more pairs or (np_col, np_row) run fewer: what a
+// caller may set is a matter of the side alone.
+static bool grid_shape_ok(const pat_plan* p, int v)
+{
+    const PlanDev& d = p->dev;
+    const bool pow2 = (d.Ng & (d.Ng - 1)) == 0;
+    if (!d.grid_spec || !pow2) return fft_shape_ok(v, sizeof(float2) * d.Ng, p->h_fft_grid, twb_bytes(p->h_fft_grid));
+    return v >= 1 && v <= 16 && v * sizeof(float2) * d.Ng + twb_bytes(p->h_fft_grid) <= kLdsMax &&
+           (v == 1 ? 2 : v) * cfft_lanes(d.Ng) <= 1024;
+}
+
 // Checks a launch configuration against the LDS, thread and width limits of
 // the kernels and, if it fits, makes it the plan's (workgroup sizes, ring
 // LDS, tile counts).  The workspace layout does not depend on it.
 int apply_launch(pat_plan* p, const LaunchCfg& c)
 {
     const PlanDev& d = p->dev;
-    // column and detector tiles of at most 32 columns / detectors (the endpoint-term sums)
-    auto fft_ok = [&](int v, size_t each, const FftDev& f, size_t fixed) {
-        return v >= 1 && v <= 16 && v * each + fixed <= kLdsMax && fft_threads(v, f) <= 1024;
-    };
-    auto grid_ok = [&](int v) {
-        const bool pow2 = (d.Ng & (d.Ng - 1)) == 0;
-        if (!d.grid_spec || !pow2) return fft_ok(v, sizeof(float2) * d.Ng, p->h_fft_grid, twb_bytes(p->h_fft_grid));
-        return v >= 1 && v <= 16 && v * sizeof(float2) * d.Ng + twb_bytes(p->h_fft_grid) <= kLdsMax &&
-               (v == 1 ? 2 : v) * cfft_lanes(d.Ng) <= 1024;
-    };
     if (c.col_np < 1 || c.col_np > 16 || c.row_rpb < 1 || c.row_rpb > 16 || c.dct_dp < 1 || c.dct_dp > 16 ||
         c.ring_rt < 1 || c.ring_rt > 64 || !gather_shape_ok(c.gat_cb, c.gat_th, c.gat_ib) ||
         !spread_shape_ok(c.spr_cb, c.spr_th, c.spr_ib))
         return PAT_ERR_ARG;
     const bool dct_ok = d.dct_spec ? (c.dct_dp * sizeof(float2) * (size_t)cfft_padded_len(2 * d.M) <= kLdsMax &&
                                       c.dct_dp * cfft_lanes(2 * d.M) <= 1024)
-                                   : fft_ok(c.dct_dp, sizeof(float2) * 2 * d.M, p->h_fft_dct, twb_bytes(p->h_fft_dct));
-    if (!grid_ok(c.col_np) || !grid_ok(c.row_rpb) || !dct_ok) return PAT_ERR_UNSUPPORTED;
+                                   : fft_shape_ok(c.dct_dp, sizeof(float2) * 2 * d.M, p->h_fft_dct, twb_bytes(p->h_fft_dct));
+    if (!grid_shape_ok(p, c.col_np) || !grid_shape_ok(p, c.row_rpb) || !dct_ok) return PAT_ERR_UNSUPPORTED;
     const size_t lr = ring_lds_bytes(d, c.ring_rt);
     if (lr > kLdsMax) return PAT_ERR_UNSUPPORTED;
     p->cfg = c;
@@ -559,7 +569,8 @@ int apply_launch(pat_plan* p, const LaunchCfg& c)
 // Default launch shapes for calls of max_batch instances.  The rules come from
 // per-kernel timings at 32^2 .. 1024^2, batch 1 .. 64 (us, in the order of the choices):
 //   column passes: the most pairs (8, 4, 2: 16 NP bytes of a row side by side) that
-//     leave a workgroup per compute unit, never fewer than 2: 1024^2 batch 8 forward /
+//     leave a workgroup per compute unit and that the plan takes (grid_shape_ok: 4 on
+//     grid sides 1728 and 1944), never fewer than 2: 1024^2 batch 8 forward /
 //     adjoint 44 / 47 at 8 pairs, 55 / 73 at 3; 256^2 one image 8.3 / 8.2 at 2, 9.9 / 9.0 at 8;
 //   row passes: waves of a workgroup share nothing, so small workgroups: 1024^2 batch 8
 //     38 / 67 at 1 row, 53 / 82 at 8;
@@ -594,7 +605,7 @@ int choose_launch(pat_plan* p, const std::vector<FftDev>& fd, int max_batch)
     const long nb = max_batch, pairs = (d.N + 1) / 2, dpairs = (d.D + 1) / 2;
     if (d.grid_spec) {
         c.col_np = 8;
-        while (c.col_np > 2 && (pairs + c.col_np - 1) / c.col_np * nb < kCus) c.col_np /= 2;
+        while (c.col_np > 2 && (!grid_shape_ok(p, c.col_np) || (pairs + c.col_np - 1) / c.col_np * nb < kCus)) c.col_np /= 2;
         c.row_rpb = d.Hy * nb >= 4 * kCus ? 2 : 1;
     } else {
         c.col_np = pick(8, sizeof(float2) * d.Ng, fg, twb_bytes(fg));
