@@ -38,14 +38,19 @@ struct SimDev {
     const int2* mask_rows;  // [Ns]: image row i keeps columns jlo <= j < jhi (support disc)
     const int2* dix;        // [D]: box cell (x, y) of each detector's stencil sample at offset 0
     const float2* dfr;      // [D]: its fractional offsets (FP64-computed)
-    // compile-time box sides (cfft.hpp): only the box rows some stencil reads are kept
+    const float2* tw;       // twiddle table of the length-M transform
+    FftDev fm;              // the length-M transform
+};
+
+// Compile-time box sides (cfft.hpp): only the box rows some stencil reads are kept.
+// Apart from SimDev, whose further 40 bytes of kernel arguments cost the run-time
+// forms of a 64^2 box 4 % (207 against 199 us at 512 samples).
+struct SimSpecDev {
     int nkeep;              // their number
     const int* keep;        // [M]: index of a box row among them, or -1
     const int* ent_ptr;     // [nkeep + 1]: the stencil rows that lie in each kept row
     const int2* ent;        // (detector, stencil row 0 .. 3)
     const float2* ctw;      // the length-M transform's table
-    const float2* tw;       // twiddle table of the length-M transform
-    FftDev fm;              // the length-M transform
 };
 
 // ---------------------------------------------------------------------------
@@ -169,7 +174,7 @@ __global__ __launch_bounds__(1024) void k_sim_rows_inv(SimDev s, float2* __restr
 }
 
 // ---------------------------------------------------------------------------
-// Compile-time box sides M (the even 2^a 3^b of 32 .. 2048).  Bound by VALU work per
+// Compile-time box sides M (the even 2^a 3^b of 216 .. 2048).  Bound by VALU work per
 // box cell and pair of samples (the phase, its cosine, the transform); at a 1152^2
 // box, per 16 pairs, the run-time forms below take 149 us (columns) and 52 us
 // (rows), these 95 and 41; the arithmetic alone would take half of the 95:
@@ -179,12 +184,27 @@ __global__ __launch_bounds__(1024) void k_sim_rows_inv(SimDev s, float2* __restr
 //   - memory goes straight into the first pass and out of the last one;
 //   - only the rows some stencil reads leave the column transforms, and the row
 //     transforms keep just their samples (x weights applied), not the rows.
+// Smaller boxes take the run-time forms: with 16 values per lane a box column is
+// 3 to 12 lanes, so a launch is few waves with long chains, where the run-time
+// forms spread it over 32 lanes a column.  Whole calls, run-time / compile-time in us,
+// at 64, 128 and 512 samples (16, 64, 256 detectors): side 64 34 / 41, 57 / 73, 199 / 277;
+// 144 47 / 51, 82 / 90, 283 / 327; 192 51 / 51, 89 / 91, 310 / 329; 216 55 / 53, 97 / 94,
+// 335 / 337; 256 56 / 51, 100 / 92, 351 / 328; 432 95 / 66, 173 / 125, 639 / 501.
 // Sequences of kSimNP neighbouring columns (or rows) are interleaved over the
 // workgroup's threads, sim_lanes(M) lanes each (16 values per lane and pass).
 // ---------------------------------------------------------------------------
 constexpr int kSimNP = 8;
 __host__ __device__ constexpr int sim_lanes(int m) { return (m + 15) / 16; }
 constexpr int sim_threads(int m) { return (kSimNP * sim_lanes(m) + 63) / 64 * 64; }
+#define PAT_SIM_LENGTHS(X) \
+    X(216) X(256) X(288) X(324) X(384) X(432) X(486) X(512) X(576) X(648) X(768) X(864) X(972) X(1024) PAT_GRID_LENGTHS_HI(X)
+constexpr bool sim_len_ok(int m)
+{
+#define PAT_CASE(LEN) if (m == LEN) return true;
+    PAT_SIM_LENGTHS(PAT_CASE)
+#undef PAT_CASE
+    return false;
+}
 
 // alpha sqrt(q) as u_hi + u_lo for q = mx^2 + my^2 (exact in two floats); see sim_phase_frac
 __device__ __forceinline__ float2 sim_phase_rate(int mx, int my, float a_hi, float a_lo)
@@ -227,7 +247,7 @@ __device__ __forceinline__ float sim_cos(float J, float2 u)
 // turn, tiles contiguous per XCD: a tile's 64 bytes of F's rows stay cached from
 // pair to pair, and the two tiles of a 128-byte line share an L2.
 template <int M>
-__global__ __launch_bounds__(sim_threads(M)) void k_sim_cols_inv_spec(SimDev s, const float2* __restrict__ F,
+__global__ __launch_bounds__(sim_threads(M)) void k_sim_cols_inv_spec(SimDev s, SimSpecDev sp, const float2* __restrict__ F,
                                                                       float2* __restrict__ Wt, int pair0, int npairs)
 {
     extern __shared__ __align__(16) float2 sm[];
@@ -243,7 +263,7 @@ __global__ __launch_bounds__(sim_threads(M)) void k_sim_cols_inv_spec(SimDev s, 
     const int ja = 2 * (pair0 + p) + 1;
     const bool has_b = ja + 1 <= s.T;
     float2* x = sm + sq * LD;
-    float2* out = Wt + (size_t)p * s.nkeep * M + c;
+    float2* out = Wt + (size_t)p * sp.nkeep * M + c;
     auto cosines = [&](int row) {  // rows up to M / 2
         const float2 u = sim_phase_rate(mx, row, s.a_hi, s.a_lo);
         return make_float2(sim_cos((float)ja, u), has_b ? sim_cos((float)(ja + 1), u) : 0.f);
@@ -273,7 +293,7 @@ __global__ __launch_bounds__(sim_threads(M)) void k_sim_cols_inv_spec(SimDev s, 
     }
     __syncthreads();
     cfft_stream<M, true, T, SyncWg, false>(
-        x, s.ctw, on, lane,
+        x, sp.ctw, on, lane,
         [&](float2 (&v)[Fst::RND][Fst::R]) {
 #pragma unroll
             for (int i = 0; i < Fst::RND; ++i)
@@ -288,7 +308,7 @@ __global__ __launch_bounds__(sim_threads(M)) void k_sim_cols_inv_spec(SimDev s, 
                 }
         },
         [&](int pos, float2 z) {
-            const int row = s.keep[pos];
+            const int row = sp.keep[pos];
             if (row >= 0) out[(size_t)row * M] = z;
         });
 }
@@ -302,7 +322,7 @@ __device__ __forceinline__ float keys_w(float t)
 
 // Inverse FFT along x of kept rows; their stencil rows' samples -> S [chunk][D][4]
 template <int M>
-__global__ __launch_bounds__(sim_threads(M)) void k_sim_rows_inv_spec(SimDev s, const float2* __restrict__ Wt,
+__global__ __launch_bounds__(sim_threads(M)) void k_sim_rows_inv_spec(SimDev s, SimSpecDev sp, const float2* __restrict__ Wt,
                                                                       float2* __restrict__ S)
 {
     extern __shared__ __align__(16) float2 sm[];
@@ -310,10 +330,10 @@ __global__ __launch_bounds__(sim_threads(M)) void k_sim_rows_inv_spec(SimDev s, 
     using Fst = cfft_first<M, T>;
     const int p = blockIdx.y, lane = threadIdx.x / kSimNP, sq = threadIdx.x % kSimNP;
     const int r0 = blockIdx.x * kSimNP, row = r0 + sq;
-    const float2* src = Wt + ((size_t)p * s.nkeep + min(row, s.nkeep - 1)) * M;
+    const float2* src = Wt + ((size_t)p * sp.nkeep + min(row, sp.nkeep - 1)) * M;
     float2* x = sm + sq * LD;
     cfft_stream<M, true, T, SyncWg, true>(
-        x, s.ctw, lane < T && row < s.nkeep, lane,
+        x, sp.ctw, lane < T && row < sp.nkeep, lane,
         [&](float2 (&v)[Fst::RND][Fst::R]) {
 #pragma unroll
             for (int i = 0; i < Fst::RND; ++i)
@@ -321,9 +341,9 @@ __global__ __launch_bounds__(sim_threads(M)) void k_sim_rows_inv_spec(SimDev s, 
                 for (int r = 0; r < Fst::R; ++r) v[i][r] = src[Fst::pos(lane, i, r)];
         },
         [&](int pos, float2 z) { x[cfft_slot<true>(pos)] = z; });
-    for (int k = 0; k < kSimNP && r0 + k < s.nkeep; ++k)
-        for (int e = s.ent_ptr[r0 + k] + threadIdx.x; e < s.ent_ptr[r0 + k + 1]; e += blockDim.x) {
-            const int2 en = s.ent[e];
+    for (int k = 0; k < kSimNP && r0 + k < sp.nkeep; ++k)
+        for (int e = sp.ent_ptr[r0 + k] + threadIdx.x; e < sp.ent_ptr[r0 + k + 1]; e += blockDim.x) {
+            const int2 en = sp.ent[e];
             const int ix = s.dix[en.x].x;
             const float fx = s.dfr[en.x].x;
             const float wx[4] = {keys_w(1.f + fx), keys_w(fx), keys_w(1.f - fx), keys_w(2.f - fx)};
@@ -362,7 +382,7 @@ __global__ __launch_bounds__(256) void k_sim_combine(SimDev s, const float2* __r
 }
 
 // ---------------------------------------------------------------------------
-// Run-time box sides (above 2048)
+// Run-time box sides (below 216 and above 2048)
 // ---------------------------------------------------------------------------
 // Samples at the detectors: thread (d, p) -> g[d][ja - 1] and g[d][jb - 1]
 __global__ __launch_bounds__(256) void k_sim_sample(SimDev s, const float2* __restrict__ Wt, float* __restrict__ g,
@@ -405,6 +425,7 @@ using pat::SimDev;
 
 struct pat_sim {
     SimDev dev;
+    pat::SimSpecDev sp;
     void* table_mem;
     int device;
     int thr_col, thr_row;       // workgroup sizes of the column and row transforms
@@ -536,7 +557,7 @@ extern "C" int pat_sim_create(const pat_plan_desc* desc, pat_sim** out)
     }
 
     // compile-time box sides: the kept rows, the stencil rows in each, the transform's table
-    s->spec = pat::grid_len_ok(M);
+    s->spec = pat::sim_len_ok(M);
     std::vector<int> keep(M, -1), eptr;
     std::vector<int2> ent;
     std::vector<float2> ctw;
@@ -546,7 +567,7 @@ extern "C" int pat_sim_create(const pat_plan_desc* desc, pat_sim** out)
             for (int a = 0; a < 4; ++a) in_row[dix[q].y - 1 + a].push_back(make_int2(q, a));
         for (int r = 0; r < M; ++r) {
             if (in_row[r].empty()) continue;
-            keep[r] = d.nkeep++;
+            keep[r] = s->sp.nkeep++;
             eptr.push_back((int)ent.size());
             ent.insert(ent.end(), in_row[r].begin(), in_row[r].end());
         }
@@ -595,10 +616,10 @@ extern "C" int pat_sim_create(const pat_plan_desc* desc, pat_sim** out)
     d.dix = (const int2*)(base + o_dix);
     d.dfr = (const float2*)(base + o_dfr);
     d.tw = (const float2*)(base + o_tw);
-    d.keep = (const int*)(base + o_keep);
-    d.ent_ptr = (const int*)(base + o_eptr);
-    d.ent = (const int2*)(base + o_ent);
-    d.ctw = (const float2*)(base + o_ctw);
+    s->sp.keep = (const int*)(base + o_keep);
+    s->sp.ent_ptr = (const int*)(base + o_eptr);
+    s->sp.ent = (const int2*)(base + o_ent);
+    s->sp.ctw = (const float2*)(base + o_ctw);
 
     // workspace: F [M][M], W [Ns][M], Wt [chunk][nrow][M]
     s->npairs = (T + 1) / 2;
@@ -647,16 +668,16 @@ extern "C" int pat_sim_run(const pat_sim* s, const float* f, float* g, void* ws,
     for (int p0 = 0; p0 < s->npairs; p0 += s->chunk) {
         const int np = std::min(s->chunk, s->npairs - p0);
         if (s->spec) {
-            const dim3 gc(pat::xcd_grid((d.M + pat::kSimNP - 1) / pat::kSimNP * np)), gr((d.nkeep + pat::kSimNP - 1) / pat::kSimNP, np);
+            const dim3 gc(pat::xcd_grid((d.M + pat::kSimNP - 1) / pat::kSimNP * np)), gr((s->sp.nkeep + pat::kSimNP - 1) / pat::kSimNP, np);
             switch (d.M) {
 #define PAT_CASE(LEN)                                                                                                 \
     case LEN: {                                                                                                       \
         const size_t lds = sizeof(float2) * (size_t)pat::kSimNP * pat::grid_col_ld(LEN);                               \
-        hipLaunchKernelGGL(pat::k_sim_cols_inv_spec<LEN>, gc, dim3(pat::sim_threads(LEN)), lds, st, d, (const float2*)F, Wt, p0, np); \
-        hipLaunchKernelGGL(pat::k_sim_rows_inv_spec<LEN>, gr, dim3(pat::sim_threads(LEN)), lds, st, d, (const float2*)Wt, Sd);    \
+        hipLaunchKernelGGL(pat::k_sim_cols_inv_spec<LEN>, gc, dim3(pat::sim_threads(LEN)), lds, st, d, s->sp, (const float2*)F, Wt, p0, np); \
+        hipLaunchKernelGGL(pat::k_sim_rows_inv_spec<LEN>, gr, dim3(pat::sim_threads(LEN)), lds, st, d, s->sp, (const float2*)Wt, Sd);    \
         break;                                                                                                        \
     }
-                PAT_GRID_LENGTHS(PAT_CASE)
+                PAT_SIM_LENGTHS(PAT_CASE)
 #undef PAT_CASE
                 default: break;
             }
