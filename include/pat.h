@@ -246,7 +246,9 @@ int  pat_stream_copy(const void* src, void* dst, size_t bytes, const int* perm, 
 
 /* Launch shapes of a plan's kernels (tile sizes; none changes the result
  * beyond the summation order of the scalar endpoint/data sums).
- * pat_plan_create picks defaults for max_batch; pat_autotune_plan measures. */
+ * pat_plan_create picks defaults for max_batch; pat_autotune_plan measures.
+ * While the interpolation's fields are the ones plan creation chose, gat_th is
+ * chosen again for each call's instances (lower tiles for fewer of them). */
 typedef struct {
     int col_np;   /* column pairs per column-pass workgroup, 1..16                           */
     int row_rpb;  /* spectrum rows per row-pass workgroup, 1..16                             */

@@ -123,7 +123,10 @@ static int forward_run(const pat_plan* p, const float* f, float* g, int batch, v
     if ((rc = check_launch())) return rc;
     prof_mark(p, 0, 2, st);
     {
-        const int cb = c.gat_cb, th = c.gat_th, ib = tile_ib(c.gat_ib, batch);
+        const int cb = c.gat_cb, ib = tile_ib(c.gat_ib, batch);
+        // a shape left at plan creation's is chosen again for the call's instances
+        const bool def = cb == 64 && c.gat_ib == 1 && c.gat_th == p->gat_th_def;
+        const int th = def ? gather_default_th(d, batch) : c.gat_th;
         const int items = ((d.Ng + cb - 1) / cb) * ((d.NB + th - 1) / th) * ((batch + ib - 1) / ib);
         const dim3 grid(xcd_grid(items));
         const size_t lds = gather_lds_bytes(cb, th, ib);

@@ -336,6 +336,7 @@ struct pat_plan {
     void* table_mem;        // one device allocation holding every table
     int n_col_tiles;        // column-pass tiles (mass partials)
     int n_pair_tiles;       // cosine-transform tiles (data-sum partials)
+    int gat_th_def;         // bands per interpolation tile that plan creation chose (for max_batch)
     int np_col, np_row;     // column pairs / rows per 2D-FFT workgroup (cfg.col_np, cfg.row_rpb as far as they fit)
     int thr_col, thr_row, thr_ring, thr_dct;  // workgroup sizes of the FFT kernels
     size_t lds_col, lds_row;  // dynamic LDS of the 2D-FFT passes
@@ -356,6 +357,8 @@ struct pat_plan {
 };
 
 namespace pat {
+int gather_default_th(const PlanDev& d, int batch);
+
 struct InstPtrs {
     char* ws;         // workspace base of instance 0
     size_t stride;    // bytes per instance

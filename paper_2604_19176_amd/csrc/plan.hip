@@ -566,6 +566,19 @@ int apply_launch(pat_plan* p, const LaunchCfg& c)
     return PAT_OK;
 }
 
+constexpr long kCus = 256;  // compute units
+
+// Bands per default interpolation tile (64 columns, one instance) of a call on
+// `batch` instances: the tallest tiles that still fill the chip, for that call's
+// instances, not the plan's capacity (128^2, one image on a plan for 64: 7 us
+// against 18 in tiles for 64 images).
+int gather_default_th(const PlanDev& d, int batch)
+{
+    int th = 16;
+    while (th > 2 && (long)((d.Ng + 63) / 64) * ((d.NB + th - 1) / th) * batch < 8 * kCus) th /= 2;
+    return th;
+}
+
 // Default launch shapes for calls of max_batch instances.  The rules come from
 // per-kernel timings at 32^2 .. 1024^2, batch 1 .. 64 (us, in the order of the choices):
 //   column passes: the most pairs (8, 4, 2: 16 NP bytes of a row side by side) that
@@ -601,7 +614,6 @@ int choose_launch(pat_plan* p, const std::vector<FftDev>& fd, int max_batch)
         if (v * bytes_each + fixed <= kLds && v * tps <= 1024) return v;
         return (bytes_each + fixed <= kLdsMax && tps <= 1024) ? 1 : 0;
     };
-    const long kCus = 256;
     const long nb = max_batch, pairs = (d.N + 1) / 2, dpairs = (d.D + 1) / 2;
     if (d.grid_spec) {
         c.col_np = 8;
@@ -614,8 +626,7 @@ int choose_launch(pat_plan* p, const std::vector<FftDev>& fd, int max_batch)
     c.dct_dp = std::min(pick(4, sizeof(float2) * 2 * d.M, fm, twb_bytes(fm)), dpairs * nb >= 4 * kCus ? 2 : 1);
     c.ring_rt = d.ring_spec && d.ring_spec_grp == 0 && d.nlam * nb <= 4 * kCus ? 2 : 1;
     c.gat_cb = 64;
-    c.gat_th = 16;
-    while (c.gat_th > 2 && (long)((d.Ng + 63) / 64) * ((d.NB + c.gat_th - 1) / c.gat_th) * nb < 8 * kCus) c.gat_th /= 2;
+    c.gat_th = p->gat_th_def = gather_default_th(d, max_batch);
     c.gat_ib = 1;
     c.spr_ib = tile_ib(4, max_batch);
     c.spr_cb = d.Ng >= 1024 ? 192 : 64;
