@@ -106,7 +106,7 @@ struct PlanDev {
     // for the interpolation and the deterministic spread
     const int* band_of;     // [npts]   ring-order index -> band-order slot
     const float4* bpt_geo;  // [npts]   (bx mod Ng as int bits, ring-order index as int bits, fx, fy)
-    const float2* bpt_phase;// [npts]   e^{-i pi (s_x + s_y)/Ng} (half-pixel shift of cell-centred pixels)
+    const float2* bpt_phase;// [npts]   e^{-i pi (s_x + s_y)/Ng}: half-pixel shift of cell-centred pixels (1 for odd N)
     const int* band_ptr;    // [NB][Ng + 1] CSR: first band-order slot with (r0, bx' >= bx)
     // spread work rows (spread_runs): a row tile is swept whole, or as S runs of
     // kSpreadTh / S bands each that write partial rows to the slab region

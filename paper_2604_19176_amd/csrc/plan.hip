@@ -964,7 +964,8 @@ static int build_tables(const pat_plan_desc* desc, const Derived& dv, pat_plan* 
             gq.z = (float)(sx - flx);
             gq.w = (float)(sy - fly);
             geo[q] = gq;
-            double a = -PI * (sx + sy) / Ng;
+            // pixel k sits at (k - floor(N/2) + 1/2) h for even N, at (k - floor(N/2)) h for odd N
+            double a = d.N % 2 == 0 ? -PI * (sx + sy) / Ng : 0.0;
             phase[q] = make_float2((float)std::cos(a), (float)std::sin(a));
             r0s[q] = r0;
             bxs[q] = bxm;
