@@ -368,8 +368,9 @@ int  pat_bessel_jn_table(int kmax, double x, double* out);
  * discretisation.  Reading for a constant speed of sound c:
  *   - the fine image (desc->n pixels a side, cell centres on [-1,1]^2, h = 2/n,
  *     pixels with centre radius >= support_r dropped) is zero-padded to a
- *     periodic box of M x M cells of the same size, centred, with M the
- *     smallest even 2^a 3^b (M - n even) whose half-width L = M h / 2 meets
+ *     periodic box of M x M cells of the same size, centred (odd n: half a
+ *     cell off the centre), with M the smallest even 2^a 3^b whose half-width
+ *     L = M h / 2 meets
  *     2 L - det_r - support_r > c t_T (no wave wraps around to a detector by
  *     the last sample t_T = n_t dt) and L > det_r + 3 h;
  *   - p(t) = IFFT2[ FFT2(f) cos(c |k| t) ] (k: the box's wave vectors), the

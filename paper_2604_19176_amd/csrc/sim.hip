@@ -458,7 +458,7 @@ long sim_box_side(int ns, double det_r, double support_r, double c, double t_las
     long m = std::max((long)std::ceil(2.0 * half / h), (long)ns);
     for (;;) {
         m = smooth_2a3b(m);
-        if (m % 2 == 0 && (m - ns) % 2 == 0) return m;
+        if (m % 2 == 0) return m;
         ++m;
     }
 }
@@ -515,8 +515,9 @@ extern "C" int pat_sim_create(const pat_plan_desc* desc, pat_sim** out)
     for (int q = 0; q < D; ++q) {
         const double th = desc->det_theta ? desc->det_theta[q]
                                           : desc->arc_center - desc->arc_span / 2 + (q + 0.5) * desc->arc_span / D;
-        const double gx = desc->det_r * std::cos(th) / h + M / 2.0 - 0.5;
-        const double gy = desc->det_r * std::sin(th) / h + M / 2.0 - 0.5;
+        // relative to the image's centre: the box's for even Ns, half a cell before it for odd
+        const double gx = desc->det_r * std::cos(th) / h + d.off + Ns / 2.0 - 0.5;
+        const double gy = desc->det_r * std::sin(th) / h + d.off + Ns / 2.0 - 0.5;
         const int ix = (int)std::floor(gx), iy = (int)std::floor(gy);
         if (ix - 1 < 0 || ix + 2 >= M || iy - 1 < 0 || iy + 2 >= M) {
             delete s;

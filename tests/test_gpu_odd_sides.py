@@ -32,3 +32,33 @@ def test_odd_sides_match_oracle(n, n_det, arc, angles, batch):
             err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
             assert err <= 1e-5, (b, err)
     plan.close()
+
+
+@pytest.mark.parametrize("n,n_det", [(17, 9), (41, 16), (121, 5)])
+def test_simulator_of_odd_sides(n, n_det):
+    """An odd image has no centred place in an even box: the detectors lie around the
+    image's centre all the same (FP64 reference with the image at the same cells)."""
+    import torch
+    import paper_2604_19176_amd as pat
+    from oracle import simulate as ref
+    geom = Geometry(n=n, n_det=n_det, n_t=35, dt=2.0 / 35, arc_span=math.radians(300.0))
+    f = np.random.default_rng(n).standard_normal((n, n))
+    sim = pat.PatSim(geom)
+    m, h = sim.box_side, 2.0 / n
+    print("odd simulator case: N=%d box %d" % (n, m), flush=True)
+    assert n < m < 6 * n and m % 2 == 0
+    x = -1.0 + (np.arange(n) + 0.5) * h
+    off = (m - n) // 2
+    box = np.zeros((m, m))
+    box[off:off + n, off:off + n] = f * (x[None, :] ** 2 + x[:, None] ** 2 < geom.support_r ** 2)
+    spec, kk = np.fft.fft2(box), ref.wavenumbers(m, h)
+    g_ref = np.empty((n_det, geom.n_t))
+    for j, t in enumerate(geom.times()):
+        p = np.fft.ifft2(spec * np.cos(kk * t)).real
+        for q, th in enumerate(geom.det_angles()):
+            gx, gy = math.cos(th) / h + off + n / 2 - 0.5, math.sin(th) / h + off + n / 2 - 0.5
+            ix, iy = math.floor(gx), math.floor(gy)
+            g_ref[q, j] = ref.keys_weights(gy - iy) @ p[iy - 1:iy + 3, ix - 1:ix + 3] @ ref.keys_weights(gx - ix)
+    g = sim.run(torch.tensor(f, dtype=torch.float32, device="cuda")).cpu().double().numpy()
+    assert np.linalg.norm(g - g_ref) <= 1e-5 * np.linalg.norm(g_ref)
+    sim.close()
