@@ -331,9 +331,10 @@ int  pat_batch_adjoint(const pat_batch* batch, const float* const* g_ptrs, float
 int  pat_batch_get_launch(const pat_batch* batch, pat_launch* out);
 int  pat_batch_set_launch(pat_batch* batch, const pat_launch* cfg);
 
-/* Autotuner.  pat_autotune_plan times candidate launch shapes of `plan` at
- * `batch` instances (1 <= batch <= max_batch) on the null stream, choosing
- * each stage's shape by its own measured kernel time, applies the fastest,
+/* Autotuner.  pat_autotune_plan times the plan's own and candidate launch
+ * shapes of `plan` at `batch` instances (1 <= batch <= max_batch) on the null
+ * stream, choosing each stage's shape by its own measured kernel time, applies
+ * the fastest,
  * then times whole forward + adjoint calls on one stream and on two (each
  * captured as a HIP graph on a stream of its own and replayed) and sets
  * the plan's split batch (pat_plan_set_split) to `batch` if two are at least

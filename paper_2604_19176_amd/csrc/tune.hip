@@ -4,8 +4,10 @@
 // kernels, so one timed forward + adjoint per round measures a candidate of
 // every stage at once: round r sets the r-th candidate of each stage's list
 // (when it fits the LDS/thread limits), and each stage keeps the candidate with
-// its smallest kernel time.  Then whole calls at the tuned shapes are timed
-// on one stream and on two (pat_plan_set_split), and two are kept if faster.
+// its smallest kernel time.  The shapes the plan came with are timed in the first
+// and in the last round, so that a stage keeps them unless a candidate is faster.
+// Then whole calls at the tuned shapes are timed on one stream and on two
+// (pat_plan_set_split), and two are kept if faster.
 // Results are cached in a small JSON file, one entry per geometry / batch /
 // device.
 #include "pat_internal.hpp"
@@ -18,7 +20,6 @@
 
 namespace {
 
-constexpr int kRounds = 10;
 constexpr int kReps = 3;  // timed repetitions per round (after one warm-up); the minimum is kept
 
 const int kColNp[] = {1, 2, 4, 8, 16};
@@ -26,15 +27,18 @@ const int kRowRpb[] = {1, 2, 4, 8, 16};
 const int kRingRt[] = {1, 2, 4};
 const int kDctDp[] = {1, 2, 4, 8};
 // (columns, rows or bands, instances per tile); a candidate whose LDS does not fit is skipped
-const int kGather[][3] = {{64, 8, 4}, {64, 16, 4}, {32, 8, 4}, {64, 4, 4}, {64, 16, 2}, {128, 16, 1},
-                          {64, 8, 1}, {128, 8, 2}, {64, 8, 2}, {32, 16, 4}};
+const int kGather[][3] = {{64, 16, 1}, {64, 8, 1}, {64, 4, 1}, {64, 2, 1}, {64, 8, 4}, {64, 16, 4}, {32, 8, 4},
+                          {64, 4, 4}, {64, 16, 2}, {128, 16, 1}, {128, 8, 2}, {64, 8, 2}, {32, 16, 4}};
 const int kSpread[][3] = {{256, 8, 4}, {192, 8, 4}, {128, 8, 4}, {256, 8, 2}, {128, 8, 2}, {192, 8, 1},
                           {128, 8, 1}, {256, 8, 1}, {64, 8, 4}, {64, 8, 1}};
 
 enum { kSCol, kSRow, kSRing, kSDct, kSGather, kSSpread, kNS };
 
+constexpr int kRounds = 13;  // the longest list
+
 // Sets the round-r candidate of stage s in c; false when the list is exhausted.
-bool set_candidate(pat_launch& c, int s, int r)
+// spr_small: the plan's spread takes only spr_ib from its shape (pat_internal.hpp).
+bool set_candidate(pat_launch& c, int s, int r, bool spr_small)
 {
     switch (s) {
         case kSCol: if (r >= 5) return false; c.col_np = kColNp[r]; return true;
@@ -42,14 +46,24 @@ bool set_candidate(pat_launch& c, int s, int r)
         case kSRing: if (r >= 3) return false; c.ring_rt = kRingRt[r]; return true;
         case kSDct: if (r >= 4) return false; c.dct_dp = kDctDp[r]; return true;
         case kSGather:
-            if (r >= 10) return false;
+            if (r >= 13) return false;
             c.gat_cb = kGather[r][0]; c.gat_th = kGather[r][1]; c.gat_ib = kGather[r][2];
             return true;
         default:
-            if (r >= 10) return false;
+            if (r >= (spr_small ? 3 : 10)) return false;
+            if (spr_small) { c.spr_ib = 1 << r; return true; }
             c.spr_cb = kSpread[r][0]; c.spr_th = kSpread[r][1]; c.spr_ib = kSpread[r][2];
             return true;
     }
+}
+
+// Entry r is the first of its columns and rows (instances of a heterogeneous batch
+// never share a tile: entries that differ in that only are the same shape there).
+bool tile_is_first(const int (*list)[3], int r)
+{
+    for (int q = 0; q < r; ++q)
+        if (list[q][0] == list[r][0] && list[q][1] == list[r][1]) return false;
+    return true;
 }
 
 void copy_stage(pat_launch& dst, const pat_launch& src, int s)
@@ -316,12 +330,14 @@ extern "C" int pat_autotune_plan(pat_plan* p, int batch, const char* cache_path)
     pat_launch best = def;
     float best_t[kNS];
     for (float& t : best_t) t = 3.0e38f;
-    for (int r = 0; r < kRounds && rc == PAT_OK; ++r) {
+    for (int r = -1; r <= kRounds && rc == PAT_OK; ++r) {  // rounds -1 and kRounds: the plan's own shapes
+        const bool own = r < 0 || r == kRounds;
         pat_launch c = def;
         bool used[kNS] = {};
         for (int s = 0; s < kNS; ++s) {
+            used[s] = own;
             pat_launch trial = def;
-            if (!set_candidate(trial, s, r)) continue;
+            if (own || !set_candidate(trial, s, r, p->dev.spr_small)) continue;
             if (pat_plan_set_launch(p, &trial) != PAT_OK) continue;  // does not fit: skip this candidate
             copy_stage(c, trial, s);
             used[s] = true;
@@ -418,10 +434,14 @@ extern "C" int pat_autotune_batch(pat_batch* b, const char* cache_path)
     pat_launch best = def;
     float best_g = 3.0e38f, best_s = 3.0e38f;
     int rc = PAT_OK;
-    for (int r = 0; r < kRounds && rc == PAT_OK; ++r) {
+    bool any_wide = false;  // an instance whose spread takes the batch's spr_cb
+    for (const pat_plan* p : b->plans) any_wide = any_wide || !p->dev.spr_small;
+    for (int r = -1; r <= kRounds && rc == PAT_OK; ++r) {  // rounds -1 and kRounds: the batch's own shapes
+        const bool own = r < 0 || r == kRounds;
         pat_launch c = def;
-        set_candidate(c, kSGather, r);
-        set_candidate(c, kSSpread, r);
+        const bool ug = own || (set_candidate(c, kSGather, r, false) && tile_is_first(kGather, r));
+        const bool us = own || (any_wide && set_candidate(c, kSSpread, r, false) && tile_is_first(kSpread, r));
+        if (!ug && !us) continue;
         if ((rc = pat_batch_set_launch(b, &c)) != PAT_OK) break;
         float tf = 3.0e38f, ta = 3.0e38f;
         for (int rep = 0; rep <= kReps && rc == PAT_OK; ++rep) {
@@ -444,8 +464,8 @@ extern "C" int pat_autotune_batch(pat_batch* b, const char* cache_path)
             ta = std::min(ta, m2);
         }
         if (rc != PAT_OK) break;
-        if (tf < best_g) { best_g = tf; copy_stage(best, c, kSGather); }
-        if (ta < best_s) { best_s = ta; copy_stage(best, c, kSSpread); }
+        if (ug && tf < best_g) { best_g = tf; copy_stage(best, c, kSGather); }
+        if (us && ta < best_s) { best_s = ta; copy_stage(best, c, kSSpread); }
     }
     for (hipEvent_t& ev : e) (void)hipEventDestroy(ev);
     if (rc != PAT_OK) {
