@@ -339,7 +339,9 @@ int  pat_batch_set_launch(pat_batch* batch, const pat_launch* cfg);
  * captured as a HIP graph on a stream of its own and replayed) and sets
  * the plan's split batch (pat_plan_set_split) to `batch` if two are at least
  * 1 % faster, else to 0; it records shapes and split in the JSON file
- * cache_path under a key made of the geometry, the batch and the device name.
+ * cache_path under a key made of the geometry, the batch, the device name and
+ * the library's version of its shape rules (entries of another version are left
+ * in the file and not used).
  * When that key is already in the file the stored shapes (and split, if the
  * entry has one) are applied without timing (an entry the shape checks now
  * reject is tuned again and replaced).

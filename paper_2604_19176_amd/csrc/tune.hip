@@ -9,7 +9,7 @@
 // Then whole calls at the tuned shapes are timed on one stream and on two
 // (pat_plan_set_split), and two are kept if faster.
 // Results are cached in a small JSON file, one entry per geometry / batch /
-// device.
+// device / version of the shape rules.
 #include "pat_internal.hpp"
 
 #include <algorithm>
@@ -78,6 +78,12 @@ void copy_stage(pat_launch& dst, const pat_launch& src, int s)
     }
 }
 
+// Part of every cache key: raised when kernels or shape rules change so that shapes
+// measured before no longer tell (such entries stay in the file, unused).
+//   2: one-instance interpolation tiles; an entry of four instances a tile, the best
+//      before, takes 109 us of interpolation at 256^2 batch 64 against 95.
+constexpr int kShapeRules = 2;
+
 std::string device_name()
 {
     int dev = 0;
@@ -105,10 +111,10 @@ std::string plan_key(const pat_plan* p, int batch)
     char buf[512];
     std::snprintf(buf, sizeof buf,
                   "plan n=%d D=%d T=%d arc=%.12g ctr=%.12g dt=%.12g c=%.12g R=%.12g rho=%.12g sig=%.12g em=%d "
-                  "angles=%016llx batch=%d dev=%s",
+                  "angles=%016llx batch=%d dev=%s rules=%d",
                   d.n, d.n_det, d.n_t, d.arc_span, d.arc_center, d.dt, d.c, d.det_r, d.support_r,
                   d.lambda_oversample, d.em_correction, (unsigned long long)angles_hash(d), batch,
-                  device_name().c_str());
+                  device_name().c_str(), kShapeRules);
     return buf;
 }
 
@@ -132,8 +138,8 @@ std::string batch_key(const pat_batch* b)
         mix(&p->cfg.ring_rt, sizeof(int)); mix(&p->cfg.dct_dp, sizeof(int));
     }
     char buf[256];
-    std::snprintf(buf, sizeof buf, "batch count=%d geo=%016llx dev=%s", b->count, (unsigned long long)h,
-                  device_name().c_str());
+    std::snprintf(buf, sizeof buf, "batch count=%d geo=%016llx dev=%s rules=%d", b->count, (unsigned long long)h,
+                  device_name().c_str(), kShapeRules);
     return buf;
 }
 

@@ -53,3 +53,22 @@ def test_the_width_a_spread_ignores_is_left_alone(width):
     plan.set_launch(spr_cb=width)
     assert plan.autotune(batch=1)["spr_cb"] == width
     plan.close()
+
+
+def test_entries_of_older_shape_rules_are_not_applied(tmp_path):
+    """A cache entry without the version of the shape rules stays in the file, unused."""
+    import json
+    import re
+    import paper_2604_19176_amd as pat
+    cache = tmp_path / "tune.json"
+    plan = pat.PatPlan(_geom(64))
+    plan.autotune(batch=1, cache_path=str(cache))
+    (key, entry), = json.loads(cache.read_text()).items()
+    old = {re.sub(r" rules=\d+$", "", key): dict(entry, gat_cb=256, gat_th=16, gat_ib=1)}
+    cache.write_text(json.dumps(old))
+    again = pat.PatPlan(_geom(64))
+    assert again.autotune(batch=1, cache_path=str(cache))["gat_cb"] != 256
+    entries = json.loads(cache.read_text())
+    assert len(entries) == 2 and set(old) < set(entries)
+    plan.close()
+    again.close()
