@@ -66,7 +66,7 @@ typedef struct {
     double lambda_oversample; /* sigma_t >= 1 (2.0); radial frequency step dlam = pi/(M c dt)         */
     int    em_correction;     /* 1: add the rank-1 endpoint term kappa*h^2*sum(m f) (default 1)       */
     int    max_batch;         /* capacity of the batch dimension (>= 1); sizes pat_workspace_size.
-                                 Plans whose points times max_batch are few take the form of the
+                                 Plans whose points times max_batch are at most 3145728 take the
                                  adjoint's spread for small launches, so plans that differ only
                                  here may differ in the last bits of A* g                          */
     const double* det_theta;  /* NULL: the uniform arc above.  Else D explicit detector angles [rad],
@@ -250,14 +250,17 @@ int  pat_stream_copy(const void* src, void* dst, size_t bytes, const int* perm, 
  * While the interpolation's fields are the ones plan creation chose, gat_th is
  * chosen again for each call's instances (lower tiles for fewer of them). */
 typedef struct {
-    int col_np;   /* column pairs per column-pass workgroup, 1..16                           */
-    int row_rpb;  /* spectrum rows per row-pass workgroup, 1..16                             */
+    int col_np;   /* column pairs per column-pass workgroup, 1..16 (grid sides up to 2048: as
+                     many of them as 1024 threads and the LDS hold, 8 above side 1024)     */
+    int row_rpb;  /* spectrum rows per row-pass workgroup, 1..16 (the same)                  */
     int ring_rt;  /* radial frequencies (rings) per ring-kernel workgroup, 1..64             */
     int dct_dp;   /* detector pairs per cosine-transform workgroup, 1..16                    */
     int gat_cb;   /* polar-interpolation tile width in grid columns: 32, 64, 128 or 256      */
     int gat_th;   /* interpolation bands (footprint base rows) per tile: 1, 2, 4, .., 64;
                      the tile window (gat_th + 7) x (gat_cb + 7) x 8 bytes is at most 64 KB  */
-    int spr_cb;   /* spread workgroup width: 64, 128, 192 or 256 columns                     */
+    int spr_cb;   /* spread workgroup width: 64, 128, 192 or 256 columns.  Plans of few points
+                     (n_points * max_batch <= 3145728) spread in tiles of 16 columns and
+                     ignore it                                                           */
     int spr_th;   /* spread rows (bands) per workgroup: always 8.  Each workgroup sweeps its
                      own 8 bands; a band's footprint reaches 7 rows further, and those
                      partial rows are completed in the adjoint row pass, so every grid
@@ -272,7 +275,9 @@ typedef struct {
  * of range, PAT_ERR_UNSUPPORTED if a tile needs more than the 160 KB of LDS
  * or the 1024 threads a workgroup can have; on error the plan is unchanged.
  * Calls already enqueued keep the shapes they were launched with.  The
- * workspace size does not depend on the launch shapes. */
+ * workspace size does not depend on the launch shapes.  The fields read back
+ * are those set, also where a kernel uses fewer (col_np, row_rpb) or ignores
+ * one (spr_cb). */
 int  pat_plan_get_launch(const pat_plan* plan, pat_launch* out);
 int  pat_plan_set_launch(pat_plan* plan, const pat_launch* cfg);
 
@@ -292,8 +297,9 @@ int  pat_plan_get_split(const pat_plan* plan, int* min_batch);
 /* Heterogeneous batch: `count` instances, each with its own plan (grid size,
  * detector count and arc, time samples may all differ; a plan may appear
  * several times).  pat_batch_forward / pat_batch_adjoint evaluate every
- * instance with one launch per stage of the operator (five per call) instead
- * of five per instance; the calls allocate nothing and do not synchronise, so
+ * instance with one launch per stage of the operator (five per call; six for
+ * an adjoint whose instances spread in both forms, see spr_cb; one more each
+ * way with explicit detector angles) instead of five per instance; the calls allocate nothing and do not synchronise, so
  * a caller can record them into a HIP graph.  Instance i uses the FFT-stage
  * tile shapes of plans[i] as they were at pat_batch_create; the interpolation
  * and spread workgroups are common to the batch (pat_batch_set_launch).
