@@ -1,4 +1,4 @@
-// cfft.hpp -- complex FFTs of compile-time length, run by one wavefront.
+// cfft.hpp -- complex FFTs of compile-time length.
 //
 // Stockham autosort passes as in fft.hpp (the pass of radix R after
 // sub-transforms of size Ns reads x[j + r n/R], multiplies input r by
@@ -7,9 +7,10 @@
 // every pass's Ns fixed at compile time: the loads and stores of a pass are
 // immediate offsets from one lane address, j mod Ns is a shift or a constant
 // multiply, and each butterfly reads its R - 1 twiddles w^{r k} from a table
-// (FP64-computed, stored FP32) instead of forming powers.  The 64 lanes of
-// wave 0 of the workgroup do the work; other waves of the workgroup only pass
-// the barriers, so the result is the same for any workgroup size.
+// (FP64-computed, stored FP32) instead of forming powers.  T lanes do a
+// sequence's work (cfft_lanes(n), more for short rings, 16 values a lane in the
+// simulator); threads past them only pass the barriers, and the arithmetic does
+// not depend on T, so the result is the same for any workgroup size.
 //
 // The radix sequence depends on the length alone (make_cplan): the plan
 // builder lays out the twiddle tables with the same function.
@@ -423,15 +424,6 @@ __device__ __forceinline__ void cfft(float2* x, const float2* __restrict__ tw, i
     static_assert(CPlanOf<N>::p.np > 0, "no compile-time plan for this length");
     static_assert(T >= cfft_lanes(N), "at least the length's lanes");
     cfft_passes<N, INV, 0, false, T>(x, tw, active, lane);
-}
-
-// One-wave lengths, computed by lanes 0..63 of wave 0.
-template <int N, bool INV>
-__device__ __forceinline__ void cfft(float2* x, const float2* __restrict__ tw)
-{
-    static_assert(cfft_lanes(N) == kCfftLanes, "one-wave lengths only");
-    const int lane = threadIdx.x;
-    cfft<N, INV>(x, tw, lane, lane < kCfftLanes);
 }
 
 // Lanes that transform a sequence of length n in a workgroup of T threads
