@@ -629,7 +629,8 @@ extern "C" int pat_batch_create(pat_plan* const* plans, int count, pat_batch** o
         I.n_pair_tiles = p->n_pair_tiles;
     }
     b->ws_bytes = off;
-    // the shapes single plans take for launches of this size (choose_launch)
+    // the interpolation shape single plans take for launches of this size
+    // (gather_default_th); the spread's width for the plans that have one
     long cells = 0;
     for (int i = 0; i < count; ++i) cells += (long)b->inst[i].d.Ng * b->inst[i].d.NB;
     b->gat_cb = 64;

@@ -1016,8 +1016,8 @@ __device__ __forceinline__ void spread_tile(const PlanDev& d, const WsLayout& L,
 // shorter chains as one lane per column x 8 bands.  For large launches the
 // lane-per-column form does less work: a point's 8 columns fill about a third
 // of the matrix operand, and float32 matrix and vector instructions share the
-// SIMD's issue.  256^2, one image: 10 us against 22 (12 before the polynomial weights); 32^2: 8.4 against 29.  1024^2,
-// batch 8: 263 against 212.
+// SIMD's issue.  256^2, one image: 12 us against 33; 32^2: 10 against 62; 256^2,
+// batch 64: 136 against 108.
 // ---------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 

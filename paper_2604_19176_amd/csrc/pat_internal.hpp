@@ -197,6 +197,13 @@ static_assert(spread_wave_words(1) >= 2 * (kSprBands + 7) * kSprCols &&
               spread_wave_words(4) >= 4 * 2 * (kSprBands + 7) * kSprCols, "a wave's output rows fit its staging area");
 // Plans whose largest call spreads at most this many points take it; above, the
 // chip is full either way and the lane-per-column form does less work per point.
+// Spread and adjoint row pass (which adds up the lane form's split tiles), us, small /
+// lane form, points in 2^20: 256^2 batch 1 (0.13) 19 / 43, 8 (1.1) 39 / 67, 16 (2.1)
+// 58 / 73, 24 (3.2) 75 / 81, 32 (4.3) 90 / 85, 64 (8.6) 165 / 148; 512^2 batch 4 (2.0)
+// 58 / 80, 6 (2.9) 93 / 90, 16 (7.8) 169 / 161; 1024^2 batch 1 (1.8) 76 / 93, 2 (3.7)
+// 104 / 110, 4 (7.4) 165 / 163.  The form is the plan's also in a heterogeneous batch,
+// so that a plan sums in one order wherever it is used: an adjoint of 4 plans of 128^2
+// takes 32 us against 65, of 16 of 256^2 130 / 135, but of 64 of them 431 / 384.
 constexpr long kSprSmallMax = 3L << 20;
 
 // Ring kernels: a ring workgroup has at least (K + 1) / kRingModesPerThread
