@@ -316,11 +316,15 @@ extern "C" int pat_tv_grad(const float* f, float* grad, float* tv, int n, int ba
 {
     if (!f || !grad || n < 2 || batch < 1 || !(eps > 0.f)) return PAT_ERR_ARG;
     hipStream_t st = (hipStream_t)stream;
-    dim3 grid((n + kTvCols - 1) / kTvCols, (n + 4 * kTvRows - 1) / (4 * kTvRows), batch);
-    hipLaunchKernelGGL(k_tv_grad, grid, dim3(256), 0, st, f, grad, n, eps * eps);
+    const int rows = tv_grad_rows((long)n * n * batch);
+    const dim3 grid((n + kTvCols - 1) / kTvCols, (n + 4 * rows - 1) / (4 * rows), batch);
+    if (rows == 1) hipLaunchKernelGGL(k_tv_grad<1>, grid, dim3(256), 0, st, f, grad, n, eps * eps);
+    else if (rows == 2) hipLaunchKernelGGL(k_tv_grad<2>, grid, dim3(256), 0, st, f, grad, n, eps * eps);
+    else hipLaunchKernelGGL(k_tv_grad<4>, grid, dim3(256), 0, st, f, grad, n, eps * eps);
     int rc = check_launch();
     if (rc || !tv) return rc;
-    hipLaunchKernelGGL(k_tv_value, dim3(batch), dim3(1024), 0, st, f, tv, n, eps * eps);
+    if (n <= 64) hipLaunchKernelGGL((k_tv_value<2, 1>), dim3(batch), dim3(1024), 0, st, f, tv, n, eps * eps);
+    else hipLaunchKernelGGL((k_tv_value<4, 2>), dim3(batch), dim3(1024), 0, st, f, tv, n, eps * eps);
     return check_launch();
 }
 

@@ -1352,29 +1352,33 @@ __global__ __launch_bounds__(CB) void k_spread_b(BatchDev bt, char* ws)
 // ---------------------------------------------------------------------------
 // total variation (smoothed, isotropic, forward differences, Neumann boundary)
 // ---------------------------------------------------------------------------
-// A wave takes 62 columns (and one beside them on either side) and kTvRows rows:
-// its loads come first, neighbours' values and quotients from the lanes beside and
-// the row above, so that a pixel's root and divisions are done once (the kernel is
-// bound by them; three evaluations per pixel before).  1024^2, batch 8:
-// 48 -> 21 us.
-constexpr int kTvRows = 4, kTvCols = 62;
+// A wave takes 62 columns (and one beside them on either side) and ROWS rows: its
+// loads come first, neighbours' values and quotients from the lanes beside and the
+// row above, so that a pixel's root and divisions are done 1 + 1 / ROWS times (three
+// times with a pixel per lane).  Large launches are bound by them: four rows; small
+// ones by the chain of one wave: one row.  us at 1 / 2 / 4 rows (a pixel per lane):
+// 256^2 2.4 / 2.6 / 3.0 (2.6), batch 4 3.1 / 3.1 / 3.4 (3.1), batch 8 4.1 / 3.8 / 4.0
+// (4.1), batch 16 6.2 / 5.5 / 5.3 (6.0); 1024^2 batch 8 29 / 23 / 21 (40).
+constexpr int kTvCols = 62;
+__host__ __device__ constexpr int tv_grad_rows(long pixels) { return pixels < 1L << 18 ? 1 : pixels < 1L << 20 ? 2 : 4; }
+template <int ROWS>
 __global__ __launch_bounds__(256) void k_tv_grad(const float* __restrict__ f, float* __restrict__ grad, int n,
                                                  float eps2)
 {
     const int b = blockIdx.z, lane = threadIdx.x & 63;
     const int j = blockIdx.x * kTvCols + lane - 1;
-    const int i0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * kTvRows;
+    const int i0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * ROWS;
     if (i0 >= n) return;
     const float* fb = f + (size_t)b * n * n;
     float* gb = grad + (size_t)b * n * n;
     const int jc = min(max(j, 0), n - 1);
-    float c[kTvRows + 2];  // rows i0 - 1 .. i0 + kTvRows
+    float c[ROWS + 2];  // rows i0 - 1 .. i0 + ROWS
 #pragma unroll
-    for (int r = 0; r < kTvRows + 2; ++r) c[r] = fb[(size_t)min(max(i0 - 1 + r, 0), n - 1) * n + jc];
+    for (int r = 0; r < ROWS + 2; ++r) c[r] = fb[(size_t)min(max(i0 - 1 + r, 0), n - 1) * n + jc];
     const bool out = lane > 0 && lane <= kTvCols && j < n;
     float up = 0.f;  // dy / s of the row above
 #pragma unroll
-    for (int r = 0; r <= kTvRows; ++r) {
+    for (int r = 0; r <= ROWS; ++r) {
         const int i = i0 - 1 + r;
         const float right = __shfl_down(c[r], 1, 64);
         const float dx = j + 1 < n ? right - c[r] : 0.f;
@@ -1391,9 +1395,12 @@ __global__ __launch_bounds__(256) void k_tv_grad(const float* __restrict__ f, fl
     }
 }
 
-// One workgroup per image: a wave takes four rows and 128 columns at a time, so that
-// the latency of its loads, which bounds it, is paid once for 512 pixels.
-// 200^2, batch 5: 29 -> 14 us (a 64-bit division per pixel before).
+// One workgroup per image: a wave takes RW rows and CW groups of 64 columns at a
+// time, so that the latency of its loads, which bounds it, is paid once for them:
+// four rows and 128 columns; images of up to 64 columns two rows and 64, which
+// leaves fewer waves and lanes idle (32^2 2.9 us, 2.9 in four rows with half the
+// lanes; 64^2 3.5 / 3.8; 200^2 13 us, 20 with a pixel per lane and a division each).
+template <int RW, int CW>
 __global__ __launch_bounds__(1024) void k_tv_value(const float* __restrict__ f, float* __restrict__ tv, int n,
                                                    float eps2)
 {
@@ -1401,25 +1408,25 @@ __global__ __launch_bounds__(1024) void k_tv_value(const float* __restrict__ f, 
     const int b = blockIdx.x;
     const float* fb = f + (size_t)b * n * n;
     const int lane = threadIdx.x & 63;
-    const int nx = (n + 127) / 128, items = nx * ((n + 3) / 4);
+    const int nx = (n + 64 * CW - 1) / (64 * CW), items = nx * ((n + RW - 1) / RW);
     float acc = 0.f;
     for (int it = threadIdx.x >> 6; it < items; it += 16) {
-        const int q = it / nx, i = 4 * q, j0 = (it - q * nx) * 128 + lane;
-        float c[5][2], r[4][2];
+        const int q = it / nx, i = RW * q, j0 = (it - q * nx) * (64 * CW) + lane;
+        float c[RW + 1][CW], r[RW][CW];
 #pragma unroll
-        for (int u = 0; u < 5; ++u) {
+        for (int u = 0; u <= RW; ++u) {
             const float* row = fb + (size_t)min(i + u, n - 1) * n;
 #pragma unroll
-            for (int v = 0; v < 2; ++v) {
+            for (int v = 0; v < CW; ++v) {
                 const int j = j0 + 64 * v;
                 c[u][v] = row[min(j, n - 1)];
-                if (u < 4) r[u][v] = row[min(j + 1, n - 1)];
+                if (u < RW) r[u][v] = row[min(j + 1, n - 1)];
             }
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < RW; ++u)
 #pragma unroll
-            for (int v = 0; v < 2; ++v) {
+            for (int v = 0; v < CW; ++v) {
                 const float dx = j0 + 64 * v + 1 < n ? r[u][v] - c[u][v] : 0.f;
                 const float dy = i + u + 1 < n ? c[u + 1][v] - c[u][v] : 0.f;
                 const float m = sqrtf(dx * dx + dy * dy + eps2);
