@@ -43,16 +43,18 @@ __device__ float block_sum(float v, float* scratch)
     return r;
 }
 
-// Sum of term(e), e < n, over the workgroup's threads, each in order (eight
-// loads in flight: one workgroup reduces an image, so it is bound by their latency)
+// Sum of term(e) (float or float2), e < n, over the workgroup's threads, each in order
+// (eight terms' loads in flight: one workgroup reduces an image, so it is bound by
+// their latency)
 template <class Term>
-__device__ __forceinline__ float strided_sum(long n, Term term)
+__device__ __forceinline__ auto strided_sum(long n, Term term)
 {
-    float acc = 0.f;
+    using V = decltype(term(0L));
+    V acc{};
     const long bd = blockDim.x;
     long e = threadIdx.x;
     for (; e + 7 * bd < n; e += 8 * bd) {
-        float v[8];
+        V v[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = term(e + u * bd);
 #pragma unroll
@@ -1532,11 +1534,13 @@ __global__ __launch_bounds__(1024) void k_pd_change(const float* __restrict__ f,
     const int b = blockIdx.x;
     const float* fb = f + (size_t)b * per;
     const float* xb = xbar + (size_t)b * per;
-    const float td = block_sum(strided_sum(per, [&](long e) {
-        const float dlt = xb[e] - fb[e];
-        return dlt * dlt;
-    }), red_s);
-    const float tf = block_sum(strided_sum(per, [&](long e) { return fb[e] * fb[e]; }), red_s);
+    // both sums in one sweep: 64^2 3.7 us, 200^2 6.3, 1024^2 85 (4.1, 8.3 and 126 with a sweep each)
+    const float2 acc = strided_sum(per, [&](long e) {
+        const float v = fb[e], dlt = xb[e] - v;
+        return make_float2(dlt * dlt, v * v);
+    });
+    const float td = block_sum(acc.x, red_s);
+    const float tf = block_sum(acc.y, red_s);
     if (threadIdx.x == 0) {
         out[2 * b] = td;
         out[2 * b + 1] = tf;
