@@ -363,8 +363,11 @@ extern "C" int pat_pd_dual_data(float* y1, const float* ax, const float* g, long
 extern "C" int pat_pd_dual_tv(float* y2, const float* xbar, int n, int batch, float sigma, float alpha, void* stream)
 {
     if (!y2 || !xbar || n < 2 || batch < 1 || !(sigma > 0.f) || !(alpha >= 0.f)) return PAT_ERR_ARG;
-    const dim3 grid((n + 63) / 64, (n + 3) / 4, batch);
-    hipLaunchKernelGGL(k_pd_dual_tv, grid, dim3(256), 0, (hipStream_t)stream, (float2*)y2, xbar, n, sigma, alpha);
+    const int w = pd_dual_cols(n, batch);
+    const dim3 grid((n + w - 1) / w, (n + 256 / w - 1) / (256 / w), batch);
+    const hipStream_t st = (hipStream_t)stream;
+    if (w == 16) hipLaunchKernelGGL(k_pd_dual_tv<16>, grid, dim3(256), 0, st, (float2*)y2, xbar, n, sigma, alpha);
+    else hipLaunchKernelGGL(k_pd_dual_tv<64>, grid, dim3(256), 0, st, (float2*)y2, xbar, n, sigma, alpha);
     return check_launch();
 }
 
@@ -372,9 +375,11 @@ extern "C" int pat_pd_primal(float* f, float* xbar, const float* aty, const floa
                              void* stream)
 {
     if (!f || !xbar || !aty || !y2 || n < 2 || batch < 1 || !(tau > 0.f)) return PAT_ERR_ARG;
-    const dim3 grid((n + 63) / 64, (n + 3) / 4, batch);
-    hipLaunchKernelGGL(k_pd_primal, grid, dim3(256), 0, (hipStream_t)stream, f, xbar, aty, (const float2*)y2, n,
-                       tau);
+    const int w = pd_primal_cols(n);
+    const dim3 grid((n + w - 1) / w, (n + 256 / w - 1) / (256 / w), batch);
+    const hipStream_t st = (hipStream_t)stream;
+    if (w == 16) hipLaunchKernelGGL(k_pd_primal<16>, grid, dim3(256), 0, st, f, xbar, aty, (const float2*)y2, n, tau);
+    else hipLaunchKernelGGL(k_pd_primal<64>, grid, dim3(256), 0, st, f, xbar, aty, (const float2*)y2, n, tau);
     return check_launch();
 }
 

@@ -1479,13 +1479,27 @@ __global__ __launch_bounds__(256) void k_pd_dual_data(float* __restrict__ y1, co
         y1[e] = (y1[e] + sigma * (ax[e] - g[e])) * inv1s;
 }
 
+// Columns of a workgroup's tile (256 / W rows of W) in the two kernels below.  Rows of
+// 64 are whole cache lines of every array: the primal step's choice for images wider
+// than a tile of 16 (us, rows of 64 / 16: 16^2 2.28 / 2.13, 32^2 2.31 / 2.45, 256^2
+// batch 8 3.6 / 4.6).  The dual step reads one row below its own: tiles of 16 rows keep
+// it in L1 where images are wide, launches small and rows start on 64-byte lines (256^2
+// batch 8 3.5 / 3.4, 512^2 2.86 / 2.75, batch 4 4.9 / 4.8, but batch 8 7.3 / 11.0; 64^2
+// 2.24 / 2.32, 300^2 batch 2 3.4 / 3.6).
+__host__ inline int pd_primal_cols(int n) { return n <= 16 ? 16 : 64; }
+__host__ inline int pd_dual_cols(int n, int batch)
+{
+    return n <= 16 || (n >= 256 && n % 16 == 0 && (long)n * n * batch <= 1L << 20) ? 16 : 64;
+}
+
 // y2 [batch][n][n] float2 (x and y components), xbar [batch][n][n]
+template <int W>
 __global__ __launch_bounds__(256) void k_pd_dual_tv(float2* __restrict__ y2, const float* __restrict__ xbar, int n,
                                                     float sigma, float alpha)
 {
     const int b = blockIdx.z;
-    const int j = blockIdx.x * 64 + (threadIdx.x & 63);  // a wave per row of 64 columns
-    const int i = blockIdx.y * 4 + (threadIdx.x >> 6);
+    const int j = blockIdx.x * W + threadIdx.x % W;
+    const int i = blockIdx.y * (256 / W) + threadIdx.x / W;
     if (i >= n || j >= n) return;
     const float* xb = xbar + (size_t)b * n * n;
     const size_t e = (size_t)b * n * n + (size_t)i * n + j;
@@ -1501,13 +1515,14 @@ __global__ __launch_bounds__(256) void k_pd_dual_tv(float2* __restrict__ y2, con
 }
 
 // f' = max(f - tau (aty + grad* y2), 0); xbar = 2 f' - f; f = f'
+template <int W>
 __global__ __launch_bounds__(256) void k_pd_primal(float* __restrict__ f, float* __restrict__ xbar,
                                                    const float* __restrict__ aty, const float2* __restrict__ y2,
                                                    int n, float tau)
 {
     const int b = blockIdx.z;
-    const int j = blockIdx.x * 64 + (threadIdx.x & 63);  // a wave per row of 64 columns
-    const int i = blockIdx.y * 4 + (threadIdx.x >> 6);
+    const int j = blockIdx.x * W + threadIdx.x % W;
+    const int i = blockIdx.y * (256 / W) + threadIdx.x / W;
     if (i >= n || j >= n) return;
     const size_t base = (size_t)b * n * n;
     const size_t e = base + (size_t)i * n + j;
