@@ -51,10 +51,12 @@ FWD_NAMES = ["colpass_fwd", "rowpass_fwd", "gather", "ring_fwd", "dct_fwd"]
 ADJ_NAMES = ["dct_adj", "ring_adj", "spread", "rowpass_adj", "colpass_adj"]
 # kernel symbols (without template arguments) of each timed stage; the
 # compile-time-length variants where a plan has them
-KERNEL_SYMBOL = {"colpass_fwd": ("k_colpass_fwd",), "rowpass_fwd": ("k_rowpass_fwd",), "gather": ("k_gather",),
+KERNEL_SYMBOL = {"colpass_fwd": ("k_colpass_fwd", "k_colpass_fwd_spec"),
+                 "rowpass_fwd": ("k_rowpass_fwd", "k_rowpass_fwd_spec"), "gather": ("k_gather",),
                  "ring_fwd": ("k_ring_fwd", "k_ring_fwd_spec"), "dct_fwd": ("k_dct_det", "k_dct_spec"),
                  "dct_adj": ("k_dct_det", "k_dct_spec"), "ring_adj": ("k_ring_adj", "k_ring_adj_spec"),
-                 "spread": ("k_spread",), "rowpass_adj": ("k_rowpass_adj",), "colpass_adj": ("k_colpass_adj",),
+                 "spread": ("k_spread", "k_spread_small"), "rowpass_adj": ("k_rowpass_adj", "k_rowpass_adj_spec"),
+                 "colpass_adj": ("k_colpass_adj", "k_colpass_adj_spec"),
                  "syn_fwd": ("k_syn_dense_fwd",), "syn_adj": ("k_syn_dense_adj",)}
 MFMA_FP32_PEAK_TFLOPS = 157.3   # dense FP32 matrix-core peak of the MI355X
 # interpolation or spread of one polar point: 16 kernel evaluations (~6 flops),
